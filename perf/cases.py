@@ -246,7 +246,11 @@ def prepare(case, seed):
 
 # -------------------------------------------------------------------- run
 class _View:
-    def __init__(self, ptr, count):
+    """One of the library's buffers, for torch; the tensor made from it holds
+    this object, and so the blocks that own the memory."""
+
+    def __init__(self, ptr, count, owner):
+        self.owner = owner
         self.__cuda_array_interface__ = dict(shape=(count,), typestr="<i4", data=(ptr, False), version=2)
 
 
@@ -272,7 +276,7 @@ def _blocks_out(st):
         where += [(v.indptr, bounds[h] + 1), (v.neighbors, edges), (v.indices, edges)]
     if st.get("where") != where:
         st["where"] = where
-        st["views"] = [torch.as_tensor(_View(p, c), device="cuda") for p, c in where]
+        st["views"] = [torch.as_tensor(_View(p, c, blocks), device="cuda") for p, c in where]
     return st["views"] + sizes
 
 
