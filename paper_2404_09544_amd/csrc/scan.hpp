@@ -167,6 +167,76 @@ __device__ __forceinline__ bool read_record(const uint64_t *rec, int64_t tile, u
     return true;
 }
 
+// The next tile of a scan launch, drawn from the ticket counter by thread 0
+// and handed to the workgroup through s_tile (one barrier); at or past ntiles
+// there is none.  With a worker per tile every worker draws once and tile
+// ntiles - 1's resets the counter; otherwise every worker draws until it
+// draws past the last tile, so exactly ntiles + workers tickets are drawn per
+// launch and the one that draws the final one resets the counter.
+__device__ __forceinline__ int64_t scan_draw_tile(uint32_t *ctl, int64_t ntiles, int64_t workers, int64_t *s_tile) {
+    if (threadIdx.x == 0) {
+        const uint32_t t = atomicAdd(&ctl[0], 1u);
+        const int64_t last = workers == ntiles ? ntiles - 1 : ntiles + workers - 1;
+        if ((int64_t)t == last) atomicExch(&ctl[0], 0u);
+        *s_tile = t;
+    }
+    __syncthreads();
+    return *s_tile;
+}
+
+// Run by a workgroup's first wavefront: publishes the tile's sum, looks back
+// for its exclusive prefix (returned on every lane) and publishes its
+// inclusive prefix.  gave_up() is called by one lane if the wait gives up.
+template <class V, class F>
+__device__ __forceinline__ V scan_look_back(uint64_t *sums, uint64_t *prefix, int64_t tile, V total, uint32_t epoch,
+                                            uint32_t *errors, uint32_t spin_limit, F &&gave_up) {
+    const int lane = threadIdx.x;
+    const uint32_t tag = epoch << 2;
+    V pre = V(0);
+    if (tile == 0) {
+        if (lane == 0) publish(prefix, 0, total, tag | 2u);
+        return pre;
+    }
+    if (lane == 0) publish(sums, tile, total, tag | 1u);
+    int64_t base = tile - 1;
+    uint32_t spins = 0;
+    while (true) {
+        if (spins >= spin_limit) {
+            if (lane == 0) {
+                atomicAdd(errors, 1u);
+                gave_up();
+            }
+            break;
+        }
+        const int64_t t = base - lane;
+        // tiles before tile 0 read as a published zero prefix; the
+        // window that reaches tile 0 always stops there first
+        V v = V(0);
+        bool is_prefix = t < 0, ready = t < 0;
+        if (t >= 0) {
+            is_prefix = read_record<V>(prefix, t, tag | 2u, v);
+            ready = is_prefix || read_record<V>(sums, t, tag | 1u, v);
+        }
+        const uint64_t pmask = __ballot(is_prefix);
+        const int pidx = pmask ? __builtin_ctzll(pmask) : kWave;
+        const uint64_t need = pidx >= kWave - 1 ? ~0ull : ((1ull << (pidx + 1)) - 1);
+        if ((__ballot(ready) & need) != need) {
+            ++spins;
+            __builtin_amdgcn_s_sleep(1);
+            continue;
+        }
+        if (lane > pidx) v = V(0);
+#pragma unroll
+        for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+        pre += v;
+        if (pidx < kWave) break;
+        base -= kWave;
+        spins = 0;
+    }
+    if (lane == 0) publish(prefix, tile, pre + total, tag | 2u);
+    return pre;
+}
+
 // An element-wise job that rides along in a scan's launch (Side::n() items,
 // Side::run(i) for each) on workgroups of its own: independent work that
 // would otherwise cost a launch of its own.
@@ -196,16 +266,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_onepass(Op op, Side side,
     const int64_t workers = ntiles < (int64_t)scan_grid ? ntiles : (int64_t)scan_grid;
     if ((int64_t)blockIdx.x >= workers) return;
     for (;;) {
-        // Every worker draws tickets until it draws one past the last tile,
-        // so exactly ntiles + workers tickets are drawn per launch; the
-        // workgroup that draws the final one resets the counter for the next.
-        if (threadIdx.x == 0) {
-            const uint32_t t = atomicAdd(&ctl[0], 1u);
-            if ((int64_t)t == ntiles + workers - 1) atomicExch(&ctl[0], 0u);
-            s_tile = t;
-        }
-        __syncthreads();
-        const int64_t tile = s_tile;
+        const int64_t tile = scan_draw_tile(ctl, ntiles, workers, &s_tile);
         if (tile >= ntiles) return;   // uniform across the workgroup
 
         const int64_t first = tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
@@ -227,51 +288,10 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_onepass(Op op, Side side,
         const V ex = block_exclusive_sum<V, kScanThreads>(s, scratch, total);
 
         if (threadIdx.x < kWave) {
-            const int lane = threadIdx.x;
-            const uint32_t tag = epoch << 2;
-            V pre = V(0);
-            if (tile == 0) {
-                if (lane == 0) publish(prefix, 0, total, tag | 2u);
-            } else {
-                if (lane == 0) publish(sums, tile, total, tag | 1u);
-                int64_t base = tile - 1;
-                uint32_t spins = 0;
-                while (true) {
-                    if (spins >= spin_limit) {
-                        if (lane == 0) {
-                            atomicAdd(errors, 1u);
-                            if constexpr (ScanHasGaveUp<Op>::value) op.gave_up();
-                        }
-                        break;
-                    }
-                    const int64_t t = base - lane;
-                    // tiles before tile 0 read as a published zero prefix; the
-                    // window that reaches tile 0 always stops there first
-                    V v = V(0);
-                    bool is_prefix = t < 0, ready = t < 0;
-                    if (t >= 0) {
-                        is_prefix = read_record<V>(prefix, t, tag | 2u, v);
-                        ready = is_prefix || read_record<V>(sums, t, tag | 1u, v);
-                    }
-                    const uint64_t pmask = __ballot(is_prefix);
-                    const int pidx = pmask ? __builtin_ctzll(pmask) : kWave;
-                    const uint64_t need = pidx >= kWave - 1 ? ~0ull : ((1ull << (pidx + 1)) - 1);
-                    if ((__ballot(ready) & need) != need) {
-                        ++spins;
-                        __builtin_amdgcn_s_sleep(1);
-                        continue;
-                    }
-                    if (lane > pidx) v = V(0);
-    #pragma unroll
-                    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-                    pre += v;
-                    if (pidx < kWave) break;
-                    base -= kWave;
-                    spins = 0;
-                }
-                if (lane == 0) publish(prefix, tile, pre + total, tag | 2u);
-            }
-            if (lane == 0) {
+            const V pre = scan_look_back<V>(sums, prefix, tile, total, epoch, errors, spin_limit, [&] {
+                if constexpr (ScanHasGaveUp<Op>::value) op.gave_up();
+            });
+            if (threadIdx.x == 0) {
                 s_prefix = pre;
                 if (tile == ntiles - 1) op.total(pre + total);
             }
@@ -284,6 +304,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_onepass(Op op, Side side,
             if (i < n) items.emit(op, j, i, run, vals[j]);
             run += vals[j];
         }
+        if (workers == ntiles) return;   // one tile per worker
         __syncthreads();   // s_tile / s_prefix are reused by the next ticket
     }
 }
