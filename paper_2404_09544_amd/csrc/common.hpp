@@ -219,7 +219,7 @@ struct DedupArgs {
 void launch_dedup(const DedupArgs &a, hipStream_t s);
 void launch_relabel(const int32_t *list, const int32_t *len_ptr, int64_t len_bound,
                     const uint64_t *map, int64_t n_nodes, const int32_t *n_frontier, int32_t *indices,
-                    hipStream_t s);
+                    const int32_t *sizes, int32_t n_sizes, int32_t *sizes_host, hipStream_t s);
 
 // gather.hip
 struct GatherArgs {

@@ -803,7 +803,7 @@ __global__ void __launch_bounds__(kScanThreads) k_union_slots(UnionArgs u, Side 
                                                               uint64_t *__restrict__ sums,
                                                               uint64_t *__restrict__ prefix,
                                                               uint32_t *__restrict__ ctl, uint32_t epoch,
-                                                              uint32_t *__restrict__ errors, uint32_t spin_limit) {
+                                                              ErrorWord errors, uint32_t spin_limit) {
     constexpr int NW = kScanThreads / kWave;
     __shared__ uint32_t wave_sum[NW];
     __shared__ int64_t s_tile;
@@ -959,11 +959,17 @@ void launch_dedup(const DedupArgs &a, hipStream_t s) {
     run_scan<DedupOp, int32_t>(op, a.len_bound, *a.scan, "dedup_scan", s);
 }
 
+// Also the last launch of a sample: with sizes_host set (device address of
+// pinned host memory) it copies the n_sizes words of `sizes` there, so the
+// synchronous sample needs no copy after it.
 __global__ void __launch_bounds__(256) k_relabel(const int32_t *__restrict__ list,
                                                  const int32_t *__restrict__ len_ptr,
                                                  const uint64_t *__restrict__ map, int64_t n_nodes,
                                                  const int32_t *__restrict__ n_frontier,
-                                                 int32_t *__restrict__ indices) {
+                                                 int32_t *__restrict__ indices, const int32_t *__restrict__ sizes,
+                                                 int32_t n_sizes, int32_t *__restrict__ sizes_host) {
+    if (sizes_host && blockIdx.x == 0 && (int32_t)threadIdx.x < n_sizes)
+        __hip_atomic_store(&sizes_host[threadIdx.x], sizes[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     const int64_t len = *len_ptr;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < len; p += stride)
@@ -971,11 +977,12 @@ __global__ void __launch_bounds__(256) k_relabel(const int32_t *__restrict__ lis
 }
 
 void launch_relabel(const int32_t *list, const int32_t *len_ptr, int64_t len_bound, const uint64_t *map,
-                    int64_t n_nodes, const int32_t *n_frontier, int32_t *indices, hipStream_t s) {
-    if (len_bound <= 0) return;
+                    int64_t n_nodes, const int32_t *n_frontier, int32_t *indices, const int32_t *sizes,
+                    int32_t n_sizes, int32_t *sizes_host, hipStream_t s) {
+    if (len_bound <= 0 && !sizes_host) return;
     KernelTimer t("relabel", s);
     hipLaunchKernelGGL(k_relabel, dim3(grid_for(len_bound, 256, 8192)), dim3(256), 0, s, list, len_ptr,
-                       map, n_nodes, n_frontier, indices);
+                       map, n_nodes, n_frontier, indices, sizes, n_sizes, sizes_host);
     GNNAV_HIP(hipGetLastError());
 }
 

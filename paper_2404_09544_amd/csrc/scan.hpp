@@ -89,9 +89,19 @@ constexpr int64_t kScanGrid = 1024;   // workgroups per scan launch, at most
 
 // Look-back polls before a wait gives up (kSpinLimit unless lowered for a
 // test; 0 gives up before the first poll, so every tile after the first
-// times out), and the device word that counts the waits that gave up (api.hip).
+// times out), and the current device's count of waits that gave up (api.hip):
+// the counter itself in device memory, and a word of pinned host memory that
+// takes each new count, so that a synchronisation point reads it without a
+// copy from the device.
 uint32_t scan_spin_limit();
-uint32_t *device_error_word();
+struct ErrorWord {
+    uint32_t *dev, *host;
+    __device__ void count() const {
+        const uint32_t n = atomicAdd(dev, 1u) + 1u;
+        __hip_atomic_store(host, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+};
+ErrorWord device_error_word();
 
 inline int64_t scan_parts(int64_t bound) {
     int64_t t = (bound + kScanTile - 1) / kScanTile;
@@ -189,7 +199,7 @@ __device__ __forceinline__ int64_t scan_draw_tile(uint32_t *ctl, int64_t ntiles,
 // inclusive prefix.  gave_up() is called by one lane if the wait gives up.
 template <class V, class F>
 __device__ __forceinline__ V scan_look_back(uint64_t *sums, uint64_t *prefix, int64_t tile, V total, uint32_t epoch,
-                                            uint32_t *errors, uint32_t spin_limit, F &&gave_up) {
+                                            const ErrorWord &errors, uint32_t spin_limit, F &&gave_up) {
     const int lane = threadIdx.x;
     const uint32_t tag = epoch << 2;
     V pre = V(0);
@@ -203,7 +213,7 @@ __device__ __forceinline__ V scan_look_back(uint64_t *sums, uint64_t *prefix, in
     while (true) {
         if (spins >= spin_limit) {
             if (lane == 0) {
-                atomicAdd(errors, 1u);
+                errors.count();
                 gave_up();
             }
             break;
@@ -250,7 +260,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_onepass(Op op, Side side,
                                                                 uint64_t *__restrict__ sums,
                                                                 uint64_t *__restrict__ prefix,
                                                                 uint32_t *__restrict__ ctl, uint32_t epoch,
-                                                                uint32_t *__restrict__ errors, uint32_t spin_limit) {
+                                                                ErrorWord errors, uint32_t spin_limit) {
     __shared__ V scratch[kScanThreads / kWave];
     __shared__ int64_t s_tile;
     __shared__ V s_prefix;
