@@ -64,7 +64,7 @@ KERNEL_SOURCES = {"aggregate_mean": ["spmm.hip", "common.hpp"],
                   "gather_rows": ["gather.hip", "common.hpp"],
                   "cache_admit": ["cache_update.hip", "scan.hpp", "common.hpp"],
                   "classify": ["gather.hip", "scan.hpp", "common.hpp"],
-                  "combine_gemm": ["gemm.hip", "common.hpp", "dma.hpp", "bf16split.hpp"],
+                  "combine_gemm": ["gemm.hip", "combine_stream.hip", "common.hpp", "dma.hpp", "bf16split.hpp"],
                   "sample_hop": ["sample.hip", "common.hpp"],
                   "dedup_first": ["sample.hip", "common.hpp"],
                   "dedup_scan": ["sample.hip", "scan.hpp", "common.hpp"],
@@ -360,7 +360,7 @@ def train_leg(args, G, g, c, wl, ws, seeds_dev, sizes_hist, torch, to_device_wei
 SIZE_SLOTS = 24      # device size array: |F_h| at [h], E_h at [17 + h] (L <= 3 fits in 24)
 
 
-SEED_TILE = 2048     # seeds the library dedups in one workgroup (one scan tile)
+SEED_TILE = 8192     # seeds the library dedups in one workgroup, first positions in LDS
 
 
 def sampling_bytes(wl, n_h, e_h, off_bytes: int, max_deg: int) -> dict:
@@ -399,8 +399,8 @@ def sampling_bytes(wl, n_h, e_h, off_bytes: int, max_deg: int) -> dict:
     out["relabel"] = e_h[L] * (4 + 8 + 4)
     out["classify"] = n_h[L] * (4 + 4 + 8)
     if slotted[0] and b0 <= SEED_TILE:
-        # seeds that fit one scan tile: first positions and their scan in one launch
-        out["dedup_scan"] += out.pop("dedup_first")
+        # one launch, and no first positions in the node table
+        out.pop("dedup_first")
     return out
 
 

@@ -299,6 +299,12 @@ void launch_aggregate_mean(const int32_t *indptr, const int32_t *indices, int64_
                            const int32_t *n_dst_dev, const void *x, int64_t ld_x, int64_t d, bool bf16, void *out,
                            int64_t ld_out, hipStream_t s, const char *label = "aggregate_mean");
 
+// combine_stream.hip
+bool combine_streams(int64_t d_in, const void *w, int64_t d_out, bool out_bf16, const void *out, int64_t ld_out);
+void launch_combine_stream(const uint16_t *self, int64_t ld_self, const uint16_t *agg, int64_t ld_agg, int64_t m,
+                           const int32_t *m_dev, int64_t d_in, const uint16_t *w, int64_t d_out, bool relu,
+                           bool out_bf16, void *out, int64_t ld_out, hipStream_t s);
+
 // gemm.hip
 int combine_kernel_kind(int64_t m, int64_t d_out, bool bf16);   // a GNNAV_COMBINE_* value
 void launch_combine(const void *self, int64_t ld_self, const void *agg, int64_t ld_agg, int64_t m,
