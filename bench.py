@@ -64,7 +64,7 @@ KERNEL_SOURCES = {"aggregate_mean": ["spmm.hip", "common.hpp"],
                   "gather_rows": ["gather.hip", "common.hpp"],
                   "cache_admit": ["cache_update.hip", "scan.hpp", "common.hpp"],
                   "classify": ["gather.hip", "scan.hpp", "common.hpp"],
-                  "combine_gemm": ["gemm.hip", "combine_stream.hip", "common.hpp", "dma.hpp", "bf16split.hpp"],
+                  "combine_gemm": ["gemm.hip", "combine_f32.hip", "combine_stream.hip", "common.hpp", "dma.hpp", "bf16split.hpp"],
                   "sample_hop": ["sample.hip", "common.hpp"],
                   "dedup_first": ["sample.hip", "common.hpp"],
                   "dedup_scan": ["sample.hip", "scan.hpp", "common.hpp"],
@@ -622,10 +622,10 @@ def kernel_entries(args, G, g, c, wl, fwd, seeds_dev, ring, link, profiled_confi
             ent["tflops"] = round(work[name] / (ms * 1e-3) / 1e12, 2)
             ent["flop_per_byte"] = round(work[name] / max(gemm_bytes.get(name, 1.0), 1.0), 1)
             if split:
-                ex = 6 * work[name] / (ms * 1e-3) / 1e12
-                ent["method"] = "fp32 products as six bf16 part products on the bf16 matrix cores"
-                ent["executed_bf16_tflops"] = round(ex, 2)
-                ent["executed_frac_of_bf16_peak"] = round(ex / MFMA_PEAK_TFLOPS["bf16"], 4)
+                ex = 3 * work[name] / (ms * 1e-3) / 1e12
+                ent["method"] = "fp32 products as three fp16 part products on the fp16 matrix cores"
+                ent["executed_f16_tflops"] = round(ex, 2)
+                ent["executed_frac_of_f16_peak"] = round(ex / MFMA_PEAK_TFLOPS["bf16"], 4)
         if name == "gather_rows":
             ent["hit_bytes_per_launch"] = round(hit_bytes / max(launches, 1), 1)
             if link_bound:
@@ -643,7 +643,7 @@ def roofline_of(kernels, name, trace_name, profiled_config):
     rec = traffic_for(name, trace_name) if profiled_config else None
     out = {"kernel": name, "bound": k["bound"], "achieved": k["achieved"], "peak": k["peak"], "unit": k["unit"],
            "frac": k["frac"], "traffic": rec.get("bytes_per_launch") if rec else None}
-    for key in ("method", "executed_bf16_tflops", "executed_frac_of_bf16_peak", "frac_of_measured_link",
+    for key in ("method", "executed_f16_tflops", "executed_frac_of_f16_peak", "frac_of_measured_link",
                 "hit_bytes_per_launch", "algorithmic_bytes_per_launch", "useful_byte_efficiency",
                 "io_read_bytes_per_launch",
                 "io_read_gbs_counted", "dram_read_bytes_per_launch", "dram_write_bytes_per_launch"):

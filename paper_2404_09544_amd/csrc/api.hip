@@ -1331,7 +1331,7 @@ static void forward_impl(gnnav_blocks *b, const void *x_dev, int64_t ld_x, const
                 h = b->act_h[l - 1].p;
             }
             launch_combine(x, ldx, agg, lda, rows, rdev, din, W_dev[l - 1], dout, bf, true, bf, h, ldh, s,
-                           kGemmLabel[tag]);
+                           kGemmLabel[tag], keep);
             x = h;
             ldx = ldh;
         } else {

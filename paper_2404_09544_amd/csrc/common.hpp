@@ -299,6 +299,14 @@ void launch_aggregate_mean(const int32_t *indptr, const int32_t *indices, int64_
                            const int32_t *n_dst_dev, const void *x, int64_t ld_x, int64_t d, bool bf16, void *out,
                            int64_t ld_out, hipStream_t s, const char *label = "aggregate_mean");
 
+// combine_f32.hip: the split weights' workspace, the launch that fills it and
+// the one that reads it
+size_t combine_f32_workspace(int64_t d_in, int64_t d_out);
+void launch_split_weights(const float *w, int64_t d_in, int64_t d_out, void *ws, hipStream_t s);
+void launch_combine_f32(const float *self, int64_t ld_self, const float *agg, int64_t ld_agg, int64_t m,
+                        const int32_t *m_dev, int64_t d_in, int64_t d_out, const void *ws, bool relu, float *out,
+                        int64_t ld_out, hipStream_t s);
+
 // combine_stream.hip
 bool combine_streams(int64_t d_in, const void *w, int64_t d_out, bool out_bf16, const void *out, int64_t ld_out);
 void launch_combine_stream(const uint16_t *self, int64_t ld_self, const uint16_t *agg, int64_t ld_agg, int64_t m,
@@ -311,6 +319,6 @@ void launch_combine(const void *self, int64_t ld_self, const void *agg, int64_t 
                     const int32_t *m_dev,
                     int64_t d_in, const void *w, int64_t d_out, bool bf16, bool relu,
                     bool out_bf16, void *out, int64_t ld_out, hipStream_t s,
-                    const char *label = "combine_gemm");
+                    const char *label = "combine_gemm", bool six_products = false);
 
 }  // namespace gnnav

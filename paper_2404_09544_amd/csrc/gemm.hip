@@ -2,8 +2,9 @@
 // self * W[0:d_in] + agg * W[d_in:2*d_in] with two A-operand pointers, so
 // the concatenation is never stored.
 //
-// Matrix cores: fp32 runs on the bf16 matrix cores through a three-way
-// bf16 split of both operands (k_combine_split, fp32-accurate; see there);
+// Matrix cores: fp32 runs on the fp16 matrix cores (combine_f32.hip) or, in
+// the hidden layers of a training step, on the bf16 matrix cores through a
+// three-way split of both operands (k_combine_split; both fp32-accurate);
 // the backward product dX = dZ * W^T (launch_matmul_bt) uses
 // v_mfma_f32_32x32x2_f32 in the ring kernel; bf16 uses
 // v_mfma_f32_32x32x16_bf16 (ring) or v_mfma_f32_16x16x32_bf16 (skinny) with
@@ -712,9 +713,9 @@ static int64_t tail_split_bands(int64_t m, int64_t n, int64_t k) {
 // rows 103 -> 101, 20902 rows 117 -> 113, 26600 rows 154 -> 138.
 static int tail_pieces(int64_t tail_tiles) { return tail_tiles <= 192 ? 3 : 2; }
 
-// fp32: the weights are split into three bf16 parts and transposed, then
-// k_combine_split runs; bf16: the weights are transposed and padded, then
-// the ring kernel runs.
+// fp32 hidden layers of a training step (see launch_combine): the weights are
+// split into three bf16 parts and transposed, then k_combine_split runs; bf16:
+// the weights are transposed and padded, then the ring kernel runs.
 template <int BM, int BN>
 static void launch_main(const void *self, int64_t ld_self, const void *agg, int64_t ld_agg, int64_t m,
                         const int32_t *m_dev, int64_t k, const void *w, int64_t n, bool bf16, bool relu,
@@ -776,6 +777,26 @@ static void launch_main(const void *self, int64_t ld_self, const void *agg, int6
 // 256 compute units.
 constexpr int64_t kSkinnyTiles = 160;
 
+// fp32 combines but those of launch_main: the weights are split into their
+// fragments, then k_combine_f32 runs (combine_f32.hip).
+static void launch_f32(const float *self, int64_t ld_self, const float *agg, int64_t ld_agg, int64_t m,
+                       const int32_t *m_dev, int64_t k, const float *w, int64_t n, bool relu, float *out, int64_t ld_out,
+                       hipStream_t s, const char *label) {
+    std::lock_guard<std::mutex> lk(g_wt.mu);
+    if (!g_wt.last_use) GNNAV_HIP(hipEventCreateWithFlags(&g_wt.last_use, hipEventDisableTiming));
+    GNNAV_HIP(hipStreamWaitEvent(s, g_wt.last_use, 0));
+    g_wt.buf.ensure(combine_f32_workspace(k, n), s);
+    {
+        KernelTimer tt("weights_transpose", s);
+        launch_split_weights(w, k, n, g_wt.buf.p, s);
+    }
+    {
+        KernelTimer tk(label, s);
+        launch_combine_f32(self, ld_self, agg, ld_agg, m, m_dev, k, n, g_wt.buf.p, relu, out, ld_out, s);
+    }
+    GNNAV_HIP(hipEventRecord(g_wt.last_use, s));
+}
+
 struct GemmChoice {
     int bm, bn;
     void (*fn)(const void *, int64_t, const void *, int64_t, int64_t, const int32_t *, int64_t, const void *,
@@ -824,9 +845,15 @@ int combine_kernel_kind(int64_t m, int64_t d_out, bool bf16) {
     return bf16 ? GNNAV_COMBINE_RING : GNNAV_COMBINE_SPLIT;
 }
 
+// six_products keeps fp32 results on k_combine_split.  A training step's hidden
+// layers ask for it: their ReLU mask is a step of the pre-activation, so one
+// value within rounding of zero (expected once in some ten million) moves the
+// weight gradients of the layer below by 1e-5, and a step resumed or repeated
+// with another rounding would leave its trajectory.  Everything else, where a
+// rounding moves results by a rounding, takes the faster kernel.
 void launch_combine(const void *self, int64_t ld_self, const void *agg, int64_t ld_agg, int64_t m,
                     const int32_t *m_dev, int64_t d_in, const void *w, int64_t d_out, bool bf16, bool relu, bool out_bf16, void *out,
-                    int64_t ld_out, hipStream_t s, const char *label) {
+                    int64_t ld_out, hipStream_t s, const char *label, bool six_products) {
     if (m <= 0) return;
     if (!bf16 && out_bf16) fail(GNNAV_E_INVALID, "bf16 output needs bf16 operands");
     if (combine_kernel_kind(m, d_out, bf16) == GNNAV_COMBINE_SKINNY) {
@@ -857,6 +884,9 @@ void launch_combine(const void *self, int64_t ld_self, const void *agg, int64_t 
         KernelTimer t(label, s);
         launch_combine_stream((const uint16_t *)self, ld_self, (const uint16_t *)agg, ld_agg, m, m_dev, d_in,
                               (const uint16_t *)w, d_out, relu, out_bf16, out, ld_out, s);
+    } else if (!bf16 && !six_products) {
+        launch_f32((const float *)self, ld_self, (const float *)agg, ld_agg, m, m_dev, d_in, (const float *)w, d_out, relu,
+                   (float *)out, ld_out, s, label);
     } else {
         const GemmChoice ch = choose_main(m, d_in, d_out, bf16);
         ch.fn(self, ld_self, agg, ld_agg, m, m_dev, d_in, w, d_out, bf16, relu, out_bf16, out, ld_out, s, label);
