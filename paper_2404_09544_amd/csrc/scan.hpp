@@ -116,7 +116,7 @@ constexpr int kRecWords = 2;   // enough for 64-bit values
 struct ScanState {
     DevBuf sums;      // uint64 [tiles][kRecWords]
     DevBuf prefix;    // uint64 [tiles][kRecWords]
-    DevBuf ctl;       // uint32 [0] ticket
+    DevBuf ctl;       // uint32 [0] ticket; [1..3] zero between launches, for other kernels' counters
     int64_t tiles = 0;
     uint32_t epoch = 0;
     void ensure(int64_t bound, hipStream_t s) {
