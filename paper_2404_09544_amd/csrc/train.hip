@@ -20,6 +20,7 @@
 //                  partial tiles are summed in range order by the reduce
 //                  kernel, which also applies W -= lr * dW
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "bf16split.hpp"
@@ -95,33 +96,64 @@ void launch_softmax_xent(const float *z, int64_t ldz, int64_t n, const int32_t *
 }
 
 // ---------------------------------------------------------------- CSC
+// Every launch here is bound by its own latency at sampled sizes (25,600 edges
+// of 24,000 columns), so the sort takes few of them: up to kCscTiles tiles the
+// scatter finds its offsets itself and counts the next pass's digits, so two
+// passes are four launches (first, scatter, scatter, column pointers; 23.5 us)
+// where separate row, histogram and scan launches made eight (47 us).
 constexpr int kSortThreads = 256;
-constexpr int kSortIters = 8;
-constexpr int kSortTile = kSortThreads * kSortIters;   // elements per workgroup
+constexpr int kSortIters = 8;          // elements of a tile per thread, at most
+constexpr int64_t kCscTiles = 64;      // tiles whose counts every scatter workgroup adds up by itself
 
-__global__ void __launch_bounds__(256) k_edge_rows(const int32_t *__restrict__ indptr, int64_t n_dst,
-                                                   const int32_t *__restrict__ n_dev, int32_t *__restrict__ rows) {
-    if (n_dev) n_dst = *n_dev;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_dst; i += stride)
-        for (int32_t p = indptr[i]; p < indptr[i + 1]; ++p) rows[p] = (int32_t)i;
+// Where the count of digit d in tile t is kept: by tile where every workgroup
+// of the scatter reads all of them, by digit where they are scanned.
+template <bool DIRECT>
+__device__ __forceinline__ int64_t hist_at(int d, int64_t t, int64_t ntiles) {
+    return DIRECT ? t * 256 + d : d * ntiles + t;
 }
 
-// Elements of tile t: t * kSortTile + it * 256 + thread, it = 0 .. 7, so a
-// workgroup meets its elements in index order, 256 at a time.
-__global__ void __launch_bounds__(256) k_radix_hist(const int32_t *__restrict__ keys, const int32_t *__restrict__ n_ptr,
-                                                    int shift, int32_t *__restrict__ hist, int64_t ntiles) {
-    __shared__ int32_t h[256];
-    const int64_t n = *n_ptr;
+// The digit counts of tile blockIdx.x: elements t * kSortThreads * ITERS +
+// it * kSortThreads + thread, so a workgroup meets its elements in index
+// order, 256 at a time.
+template <int ITERS, bool DIRECT>
+__device__ __forceinline__ void tile_hist(const int32_t *keys, int64_t n, int shift, int32_t *hist, int64_t ntiles,
+                                          int32_t *h) {
     h[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kSortTile;
-    for (int it = 0; it < kSortIters; ++it) {
+    const int64_t base = (int64_t)blockIdx.x * (kSortThreads * ITERS);
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it) {
         const int64_t e = base + it * kSortThreads + threadIdx.x;
         if (e < n) atomicAdd(&h[(keys[e] >> shift) & 255], 1);
     }
     __syncthreads();
-    hist[(int64_t)threadIdx.x * ntiles + blockIdx.x] = h[threadIdx.x];
+    hist[hist_at<DIRECT>(threadIdx.x, blockIdx.x, ntiles)] = h[threadIdx.x];
+}
+
+// The first pass's counts, and on the workgroups past the tiles the row of
+// every edge and zeros for the later passes' counts.
+template <int ITERS, bool DIRECT>
+__global__ void __launch_bounds__(256) k_csc_first(const int32_t *__restrict__ indptr, int64_t n_dst,
+                                                   const int32_t *__restrict__ n_dev, int32_t *__restrict__ rows,
+                                                   const int32_t *__restrict__ keys, const int32_t *__restrict__ n_ptr,
+                                                   int32_t *__restrict__ hist, int64_t ntiles, int64_t zeros) {
+    __shared__ int32_t h[256];
+    if (blockIdx.x < ntiles) {
+        tile_hist<ITERS, DIRECT>(keys, *n_ptr, 0, hist, ntiles, h);
+        return;
+    }
+    if (n_dev) n_dst = *n_dev;
+    const int64_t stride = (int64_t)(gridDim.x - ntiles) * blockDim.x;
+    const int64_t first = (int64_t)(blockIdx.x - ntiles) * blockDim.x + threadIdx.x;
+    for (int64_t i = first; i < zeros; i += stride) hist[256 * ntiles + i] = 0;
+    for (int64_t i = first; i < n_dst; i += stride)
+        for (int32_t p = indptr[i]; p < indptr[i + 1]; ++p) rows[p] = (int32_t)i;
+}
+
+__global__ void __launch_bounds__(256) k_radix_hist(const int32_t *__restrict__ keys, const int32_t *__restrict__ n_ptr,
+                                                    int shift, int32_t *__restrict__ hist, int64_t ntiles) {
+    __shared__ int32_t h[256];
+    tile_hist<kSortIters, false>(keys, *n_ptr, shift, hist, ntiles, h);
 }
 
 struct HistScanOp {
@@ -137,27 +169,55 @@ struct HistScanOp {
 // Stable scatter: an element's destination is its digit's offset for this
 // tile, plus the elements of the same digit earlier in the tile.  Within a
 // wavefront the earlier same-digit lanes come from eight ballots (one per
-// digit bit); across the four wavefronts and the eight passes, from LDS
-// counters.
+// digit bit); across the four wavefronts and the passes over the tile, from
+// LDS counters.  The offsets are given (offs), or, with DIRECT, added up from
+// all tiles' counts; then also the next pass's counts, by output tile, are
+// added to hist_next (nullptr: this is the last pass): one addition for all
+// lanes that share the counter.  The lanes of a digit go to consecutive
+// places, which lie in at most two tiles.
+template <int ITERS, bool DIRECT>
 __global__ void __launch_bounds__(256) k_radix_scatter(const int32_t *__restrict__ keys_in,
                                                        const int32_t *__restrict__ vals_in,
                                                        const int32_t *__restrict__ n_ptr, int shift,
                                                        const int32_t *__restrict__ offs, int64_t ntiles,
-                                                       int32_t *__restrict__ keys_out, int32_t *__restrict__ vals_out) {
+                                                       int32_t *__restrict__ keys_out, int32_t *__restrict__ vals_out,
+                                                       int32_t *__restrict__ hist_next) {
+    constexpr int TILE = kSortThreads * ITERS;
     __shared__ int32_t run[256];
     __shared__ int32_t cnt[kSortThreads / kWave][256];
     const int64_t n = *n_ptr;
     const int lane = lane_id(), wid = threadIdx.x / kWave;
-    run[threadIdx.x] = offs[(int64_t)threadIdx.x * ntiles + blockIdx.x];
+    const int64_t base = (int64_t)blockIdx.x * TILE;
+    int32_t keys[ITERS], vals[ITERS];
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it) {
+        const int64_t e = base + it * kSortThreads + threadIdx.x;
+        keys[it] = e < n ? keys_in[e] : 0;
+        vals[it] = e < n ? vals_in[e] : 0;
+    }
+    if constexpr (DIRECT) {
+        int32_t all = 0, before = 0;
+#pragma unroll 8
+        for (int t = 0; t < (int)ntiles; ++t) {
+            const int32_t c = offs[t * 256 + threadIdx.x];
+            all += c;
+            before += t < (int)blockIdx.x ? c : 0;
+        }
+        __shared__ int32_t scratch[kSortThreads / kWave];
+        int32_t total;
+        run[threadIdx.x] = block_exclusive_sum<int32_t, kSortThreads>(all, scratch, total) + before;
+    } else {
+        run[threadIdx.x] = offs[(int64_t)threadIdx.x * ntiles + blockIdx.x];
+    }
     const uint64_t below = (1ull << lane) - 1ull;
-    const int64_t base = (int64_t)blockIdx.x * kSortTile;
-    for (int it = 0; it < kSortIters; ++it) {
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it) {
 #pragma unroll
         for (int w = 0; w < kSortThreads / kWave; ++w) cnt[w][threadIdx.x] = 0;
         __syncthreads();
         const int64_t e = base + it * kSortThreads + threadIdx.x;
         const bool valid = e < n;
-        const int32_t key = valid ? keys_in[e] : 0;
+        const int32_t key = keys[it];
         const int d = (key >> shift) & 255;
         uint64_t m = __ballot(valid);
 #pragma unroll
@@ -168,11 +228,24 @@ __global__ void __launch_bounds__(256) k_radix_scatter(const int32_t *__restrict
         const int rank = __popcll(m & below);
         if (valid && rank == 0) cnt[wid][d] = __popcll(m);
         __syncthreads();
+        int32_t pos = run[d] + rank;
+        for (int w = 0; w < wid; ++w) pos += cnt[w][d];
         if (valid) {
-            int32_t pos = run[d] + rank;
-            for (int w = 0; w < wid; ++w) pos += cnt[w][d];
             keys_out[pos] = key;
-            vals_out[pos] = vals_in[e];
+            vals_out[pos] = vals[it];
+        }
+        if constexpr (DIRECT) {
+            if (hist_next) {
+                const int next = (key >> (shift + 8)) & 255, tile = pos / TILE;
+#pragma unroll
+                for (int bit = 0; bit < 8; ++bit) {
+                    const uint64_t ones = __ballot((next >> bit) & 1);
+                    m &= ((next >> bit) & 1) ? ones : ~ones;
+                }
+                const uint64_t odd = __ballot(tile & 1);
+                m &= (tile & 1) ? odd : ~odd;
+                if (valid && (m & below) == 0) atomicAdd(&hist_next[tile * 256 + next], __popcll(m));
+            }
         }
         __syncthreads();
         int32_t add = 0;
@@ -209,35 +282,58 @@ void CscWorkspace::build(const int32_t *indptr, const int32_t *indices, int64_t 
                          hipStream_t s, const char *label) {
     KernelTimer t(label, s);
     const int64_t eb = std::max<int64_t>(e_bound, 1);
-    const int64_t ntiles = (eb + kSortTile - 1) / kSortTile;
+    int bits = 1;
+    while (bits < 31 && (int64_t(1) << bits) < n_src_bound) ++bits;
+    const int passes = (bits + 7) / 8;
+    // the smallest tiles of which there are at most kCscTiles; past that (64
+    // tiles of 2,048) the counts are scanned by launches of their own
+    int iters = 1;
+    while (iters < kSortIters && eb > kCscTiles * kSortThreads * iters) iters *= 2;
+    const int64_t tile = (int64_t)kSortThreads * iters, ntiles = (eb + tile - 1) / tile;
+    const bool direct = ntiles <= kCscTiles;
     for (int k = 0; k < 2; ++k) {
         keys[k].ensure(eb * sizeof(int32_t), s);
         vals[k].ensure(eb * sizeof(int32_t), s);
     }
-    hist.ensure(256 * ntiles * sizeof(int32_t), s);
-    offs.ensure(256 * ntiles * sizeof(int32_t), s);
+    hist.ensure((direct ? passes : 1) * 256 * ntiles * sizeof(int32_t), s);
+    if (!direct) {
+        offs.ensure(256 * ntiles * sizeof(int32_t), s);
+        scan.ensure(256 * ntiles, s);
+    }
     col_ptr.ensure((n_src_bound + 1) * sizeof(int32_t), s);
     // pass 0 reads the block's indices directly; values are destination rows
-    hipLaunchKernelGGL(k_edge_rows, dim3(grid_for(n_dst, 256, 4096)), dim3(256), 0, s, indptr, n_dst, n_dst_dev,
-                       vals[1].as<int32_t>());
-    int bits = 1;
-    while (bits < 31 && (int64_t(1) << bits) < n_src_bound) ++bits;
-    const int passes = (bits + 7) / 8;
     const int32_t *kin = indices, *vin = vals[1].as<int32_t>();
-    int cur = 0;
-    scan.ensure(256 * ntiles, s);
-    for (int p = 0; p < passes; ++p) {
-        int32_t *kout = keys[cur].as<int32_t>(), *vout = vals[cur].as<int32_t>();
-        hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)ntiles), dim3(256), 0, s, kin, n_edges_dev, 8 * p,
-                           hist.as<int32_t>(), ntiles);
-        run_scan<HistScanOp, int32_t>(HistScanOp{hist.as<int32_t>(), offs.as<int32_t>(), 256 * ntiles},
-                                      256 * ntiles, scan, "csc_scan", s);
-        hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)ntiles), dim3(256), 0, s, kin, vin, n_edges_dev, 8 * p,
-                           offs.as<int32_t>(), ntiles, kout, vout);
-        kin = kout;
-        vin = vout;
-        cur ^= 1;
-    }
+    int32_t *h = hist.as<int32_t>();
+    const int64_t zeros = direct ? (passes - 1) * 256 * ntiles : 0;
+    const unsigned first_grid = (unsigned)(ntiles + grid_for(std::max(n_dst, zeros), 256, 4096));
+    auto run = [&](auto iters_, auto direct_) {
+        constexpr int IT = decltype(iters_)::value;
+        constexpr bool DIRECT = decltype(direct_)::value;
+        hipLaunchKernelGGL((k_csc_first<IT, DIRECT>), dim3(first_grid), dim3(256), 0, s, indptr, n_dst, n_dst_dev,
+                           vals[1].as<int32_t>(), indices, n_edges_dev, h, ntiles, zeros);
+        for (int p = 0; p < passes; ++p) {
+            int32_t *kout = keys[p & 1].as<int32_t>(), *vout = vals[p & 1].as<int32_t>();
+            const int32_t *at = h + p * 256 * ntiles;
+            if constexpr (!DIRECT) {
+                if (p > 0)
+                    hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)ntiles), dim3(256), 0, s, kin, n_edges_dev, 8 * p,
+                                       h, ntiles);
+                run_scan<HistScanOp, int32_t>(HistScanOp{h, offs.as<int32_t>(), 256 * ntiles}, 256 * ntiles, scan,
+                                              "csc_scan", s);
+                at = offs.as<int32_t>();
+            }
+            hipLaunchKernelGGL((k_radix_scatter<IT, DIRECT>), dim3((unsigned)ntiles), dim3(256), 0, s, kin, vin,
+                               n_edges_dev, 8 * p, at, ntiles, kout, vout,
+                               DIRECT && p + 1 < passes ? h + (p + 1) * 256 * ntiles : nullptr);
+            kin = kout;
+            vin = vout;
+        }
+    };
+    if (!direct) run(std::integral_constant<int, kSortIters>(), std::false_type());
+    else if (iters == 1) run(std::integral_constant<int, 1>(), std::true_type());
+    else if (iters == 2) run(std::integral_constant<int, 2>(), std::true_type());
+    else if (iters == 4) run(std::integral_constant<int, 4>(), std::true_type());
+    else run(std::integral_constant<int, 8>(), std::true_type());
     sorted_rows = vin;
     hipLaunchKernelGGL(k_col_ptr, dim3(grid_for(n_src_bound + 1, 256, 4096)), dim3(256), 0, s, kin, n_edges_dev,
                        n_src_bound, col_ptr.as<int32_t>());
