@@ -266,6 +266,14 @@ struct CscWorkspace {
         col_ptr.release();
     }
 };
+// The batch loss: the mean of the rows' losses (out nullptr: none).
+struct LossMean {
+    const float *row_loss = nullptr;
+    int64_t n = 0;
+    const int32_t *n_dev = nullptr;
+    float *out = nullptr;
+};
+// loss nullptr: the row losses only.
 void launch_softmax_xent(const float *z, int64_t ldz, int64_t n, const int32_t *n_dev, int64_t C,
                          const int32_t *nodes, const int32_t *labels, float *dz, int64_t lddz, float *row_loss,
                          float *loss, hipStream_t s);
@@ -275,7 +283,8 @@ void launch_aggregate_t(const CscWorkspace &csc, const int32_t *indptr, int64_t 
                         float *out, int64_t ld_out, hipStream_t s, const char *label);
 void launch_wgrad(const float *x_self, int64_t ld_self, const float *agg, int64_t ld_agg, int64_t m,
                   const int32_t *m_dev, int64_t d_in, const float *dz, int64_t ld_dz, int64_t d_out, DevBuf &part,
-                  float *dw, float *w, float lr, hipStream_t s, const char *label);
+                  float *dw, float *w, float lr, hipStream_t s, const char *label,
+                  const LossMean &loss = LossMean());
 
 // cache_update.hip: the cache's update policies over the ring of dynamic
 // slots [lo, lo + rn), run after a gather on its lists and output.

@@ -63,22 +63,23 @@ __global__ void __launch_bounds__(256) k_softmax_xent(const float *__restrict__ 
     }
 }
 
-// One workgroup: thread t sums rows t, t + 256, ... in double; the partial
-// sums are combined by a fixed tree.
-__global__ void __launch_bounds__(256) k_loss_mean(const float *__restrict__ row_loss, int64_t n,
-                                                   const int32_t *__restrict__ n_dev, float *__restrict__ out) {
+// Run by one workgroup: thread t sums rows t, t + 256, ... in double; the
+// partial sums are combined by a fixed tree.
+__device__ void loss_mean(const LossMean &l) {
     __shared__ double part[256];
-    if (n_dev) n = *n_dev;
+    const int64_t n = l.n_dev ? *l.n_dev : l.n;
     double s = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += 256) s += (double)row_loss[i];
+    for (int64_t i = threadIdx.x; i < n; i += 256) s += (double)l.row_loss[i];
     part[threadIdx.x] = s;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[0] = n > 0 ? (float)(part[0] / (double)n) : 0.0f;
+    if (threadIdx.x == 0) l.out[0] = n > 0 ? (float)(part[0] / (double)n) : 0.0f;
 }
+
+__global__ void __launch_bounds__(256) k_loss_mean(LossMean l) { loss_mean(l); }
 
 void launch_softmax_xent(const float *z, int64_t ldz, int64_t n, const int32_t *n_dev, int64_t C,
                          const int32_t *nodes, const int32_t *labels, float *dz, int64_t lddz, float *row_loss,
@@ -88,9 +89,9 @@ void launch_softmax_xent(const float *z, int64_t ldz, int64_t n, const int32_t *
         hipLaunchKernelGGL(k_softmax_xent, dim3(grid_for(n, 4, 4096)), dim3(256), 0, s, z, ldz, n, n_dev, C, nodes,
                            labels, dz, lddz, row_loss);
     }
-    {
+    if (loss) {
         KernelTimer t("loss_mean", s);
-        hipLaunchKernelGGL(k_loss_mean, dim3(1), dim3(256), 0, s, row_loss, n, n_dev, loss);
+        hipLaunchKernelGGL(k_loss_mean, dim3(1), dim3(256), 0, s, LossMean{row_loss, n, n_dev, loss});
     }
     GNNAV_HIP(hipGetLastError());
 }
@@ -103,7 +104,11 @@ void launch_softmax_xent(const float *z, int64_t ldz, int64_t n, const int32_t *
 // where separate row, histogram and scan launches made eight (47 us).
 constexpr int kSortThreads = 256;
 constexpr int kSortIters = 8;          // elements of a tile per thread, at most
-constexpr int64_t kCscTiles = 64;      // tiles whose counts every scatter workgroup adds up by itself
+// Tiles whose counts every scatter workgroup adds up by itself.  The adjoint
+// of 30,000 edges took 55.1 / 50.4 / 48.8 / 53.1 us with at most 16 / 32 / 64 /
+// 128, of 64,000 63.2 / 54.4 / 54.3 / 55.8, of 262,000 88.8 with scans and 99.9
+// without (128 tiles).
+constexpr int64_t kCscTiles = 64;
 
 // Where the count of digit d in tile t is kept: by tile where every workgroup
 // of the scatter reads all of them, by digit where they are scanned.
@@ -584,12 +589,20 @@ __global__ void __launch_bounds__(256) k_wgrad_split(const float *__restrict__ X
 // dW = sum of the split partials in split order; optionally copied out, and
 // W -= lr * dW when lr != 0.  V = 4: four consecutive elements per lane
 // (16-byte loads; total, dw and w 16-byte aligned).  The partials' loads go
-// out eight at a time ahead of their adds, which keep the split order.
+// out eight at a time ahead of their adds, which keep the split order.  With
+// loss.out set, the last workgroup takes the batch loss instead (a launch of
+// its own is 4.6 us).
 template <int V>
 __global__ void __launch_bounds__(256) k_wgrad_reduce(const float *__restrict__ part, int64_t total, int64_t splits,
-                                                      float *__restrict__ dw, float *__restrict__ w, float lr) {
+                                                      float *__restrict__ dw, float *__restrict__ w, float lr,
+                                                      LossMean loss) {
     typedef float fv __attribute__((ext_vector_type(V)));
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x, nv = total / V;
+    const int64_t wgs = gridDim.x - (loss.out ? 1 : 0);
+    if (blockIdx.x == wgs) {
+        loss_mean(loss);
+        return;
+    }
+    const int64_t stride = wgs * blockDim.x, nv = total / V;
     const fv *pv = (const fv *)part;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += stride) {
         fv g = (fv)0.0f;
@@ -613,18 +626,20 @@ __global__ void __launch_bounds__(256) k_wgrad_reduce(const float *__restrict__ 
 
 void launch_wgrad(const float *x_self, int64_t ld_self, const float *agg, int64_t ld_agg, int64_t m,
                   const int32_t *m_dev, int64_t d_in, const float *dz, int64_t ld_dz, int64_t d_out, DevBuf &part,
-                  float *dw, float *w, float lr, hipStream_t s, const char *label) {
+                  float *dw, float *w, float lr, hipStream_t s, const char *label, const LossMean &loss) {
     auto a16 = [](const void *p, int64_t ld) { return (((uintptr_t)p & 15u) == 0) && ld % 4 == 0; };
     if (!(a16(x_self, ld_self) && a16(agg, ld_agg) && a16(dz, ld_dz)))
         fail(GNNAV_E_INVALID, "weight gradient operands need 16-byte aligned rows");
     // 128 x 128 tiles (128 x 64 for outputs at most 64 wide); the row range
     // is split so that at most 512 workgroups run, two per compute unit all
     // at once (rounding up left a few for a second round: 233k layer 1 with
-    // 20 tiles ran 520)
+    // 20 tiles ran 520).  A split has at least 64 rows, two steps: with few
+    // tiles the launch is as long as one workgroup's chain of steps (1,024 x
+    // 2 x 256 x 41, 4 tiles: 13.7 us with at least 256 rows a split, 7.0 so)
     const int64_t BA = 128, BO = d_out > 64 ? 128 : 64;
     const int64_t tiles = 2 * ((d_in + BA - 1) / BA) * ((d_out + BO - 1) / BO);
     int64_t splits = 512 / tiles;
-    splits = std::min<int64_t>(splits, std::max<int64_t>(1, (m + 255) / 256));
+    splits = std::min<int64_t>(splits, std::max<int64_t>(1, (m + 63) / 64));
     splits = std::max<int64_t>(1, std::min<int64_t>(splits, 64));
     const int64_t total = 2 * d_in * d_out;
     part.ensure((size_t)(splits * total) * sizeof(float), s);
@@ -642,12 +657,13 @@ void launch_wgrad(const float *x_self, int64_t ld_self, const float *agg, int64_
     {
         KernelTimer t("wgrad_reduce", s);
         const bool vec = total % 4 == 0 && ((uintptr_t)dw & 15u) == 0 && ((uintptr_t)w & 15u) == 0;
+        const unsigned extra = loss.out ? 1 : 0;
         if (vec)
-            hipLaunchKernelGGL(k_wgrad_reduce<4>, dim3(grid_for(total / 4, 256, 1024)), dim3(256), 0, s,
-                               part.as<float>(), total, splits, dw, w, lr);
+            hipLaunchKernelGGL(k_wgrad_reduce<4>, dim3(grid_for(total / 4, 256, 1024) + extra), dim3(256), 0, s,
+                               part.as<float>(), total, splits, dw, w, lr, loss);
         else
-            hipLaunchKernelGGL(k_wgrad_reduce<1>, dim3(grid_for(total, 256, 1024)), dim3(256), 0, s,
-                               part.as<float>(), total, splits, dw, w, lr);
+            hipLaunchKernelGGL(k_wgrad_reduce<1>, dim3(grid_for(total, 256, 1024) + extra), dim3(256), 0, s,
+                               part.as<float>(), total, splits, dw, w, lr, loss);
     }
     GNNAV_HIP(hipGetLastError());
 }
