@@ -474,6 +474,98 @@ __global__ void __launch_bounds__(256) k_sample_biased(const OffT *__restrict__ 
     }
 }
 
+// The same selection on a partitioned column array for 0 < k <= G <= 32: G
+// lanes per row, 64 / G rows per wavefront (as k_sample_group).  Bound by the
+// chain of loads and steps of a row, so rows side by side in a wavefront take
+// no longer than one: a second hop's 24,000 rows at fan-out 10 took 15.1 us a
+// wavefront per row, 10.2 so; 1,024 rows at fan-out 25 take 9.2 either way.
+template <class OffT, int G>
+__global__ void __launch_bounds__(256) k_sample_biased_group(const OffT *__restrict__ row_ptr,
+                                                             const int32_t *__restrict__ col,
+                                                             const int32_t *__restrict__ nodes,
+                                                             const int32_t *__restrict__ n_prev,
+                                                             const int32_t *__restrict__ indptr,
+                                                             int32_t *__restrict__ out, int32_t k, uint32_t key0,
+                                                             uint32_t key1, uint32_t hop, uint32_t eta,
+                                                             const int32_t *__restrict__ part_col,
+                                                             const int32_t *__restrict__ part_cnt,
+                                                             unsigned long long *__restrict__ first, uint32_t tag,
+                                                             int32_t stride, int64_t n_nodes) {
+    constexpr int R = kWave / G;
+    const int lane = lane_id(), r = lane / G, gl = lane % G;
+    const int64_t n_rows = *n_prev;
+    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
+    for (int64_t base = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave * R; base < n_rows;
+         base += nwaves * R) {
+        const int64_t i = base + r;
+        const bool valid = i < n_rows;
+        int32_t v = 0;
+        int64_t start = 0, deg = 0, at = 0, c = 0;
+        if (valid) {
+            v = nodes[i];
+            deg = frontier_degree(row_ptr, v, n_nodes, start);
+            at = stride ? i * stride : (int64_t)indptr[i];
+        }
+        const bool draw = valid && deg > k;
+        uint32_t w[4] = {0u, 0u, 0u, 0u};
+        if (draw) {
+            c = part_cnt[v];
+            philox4((uint32_t)gl, (uint32_t)v, 0u, hop, key0, key1, w);
+        }
+        const int64_t u = deg - c;
+        // 1. classes; while a row's weights stay below 2^32, one 32-bit
+        // product gives the same t
+        const uint64_t weight = (uint64_t)eta * (uint64_t)c + (uint64_t)u;
+        const uint32_t x1 = w[1];
+        int32_t kc = 0;
+        if (__ballot(weight >> 32 != 0) == 0) {
+            uint32_t heavy = eta * (uint32_t)c, b = (uint32_t)weight;
+            for (int j = 0; j < k; ++j) {
+                const uint32_t t = __umulhi((uint32_t)__shfl((int)x1, j, G), b);
+                const bool cached = t < heavy;
+                kc += cached;
+                b -= cached ? eta : 1u;
+                heavy -= cached ? eta : 0u;
+            }
+        } else {
+            uint64_t heavy = (uint64_t)eta * (uint64_t)c, b = weight;
+            for (int j = 0; j < k; ++j) {
+                const uint64_t x = (uint32_t)__shfl((int)x1, j, G);
+                const uint64_t t = x * (b >> 32) + ((x * (b & 0xffffffffull)) >> 32);
+                const bool cached = t < heavy;
+                kc += cached;
+                b -= cached ? eta : 1u;
+                heavy -= cached ? eta : 0u;
+            }
+        }
+        // 2. Floyd inside each class
+        const bool cached_lane = gl < kc;
+        const int32_t step = cached_lane ? gl : gl - kc;
+        uint32_t t = 0, m = 0;
+        if (draw && gl < k) {
+            philox4((uint32_t)step, (uint32_t)v, 0u, hop, key0, key1, w);
+            m = (uint32_t)((cached_lane ? c - kc : u - (k - kc)) + step);
+            t = __umulhi(cached_lane ? w[2] : w[3], m + 1u);
+        }
+        uint32_t pick = t;
+        for (int j = 1; j < k; ++j) {
+            const uint32_t tj = (uint32_t)__shfl((int)t, j, G);
+            const bool same = cached_lane == (j < kc);
+            const uint64_t clash = (__ballot(same && gl < j && pick == tj) >> (r * G)) & ((1ull << j) - 1ull);
+            if (gl == j && clash != 0) pick = m;
+        }
+        // 3. class index -> row offset
+        const bool writes = draw ? gl < k : (valid && gl < deg);
+        if (writes) {
+            const int32_t id = draw ? part_col[start + (cached_lane ? 0 : c) + pick] : col[start + gl];
+            out[at + gl] = id;
+            note_first(first, tag, id, at + gl);
+        } else if (valid && gl < stride) {
+            out[at + gl] = -1;
+        }
+    }
+}
+
 // Each row's neighbours split into cached then uncached, CSR order kept
 // within each class; part_cnt[v] = cached neighbours of v.  One wavefront
 // per row: a ballot per 64 neighbours gives every lane its rank in its class.
@@ -533,16 +625,31 @@ void launch_sample_hop(const SampleHopArgs &a, hipStream_t s) {
         const uint32_t key0 = (uint32_t)(a.rng_seed & 0xffffffffu), key1 = (uint32_t)(a.rng_seed >> 32);
         const unsigned grid = grid_for(a.rows_bound, 256 / kWave, 16384);
         KernelTimer t("sample_hop", s);
+        auto first = (unsigned long long *)a.first_map;
+        auto run = [&](auto row_ptr) {
+            using OffT = std::remove_const_t<std::remove_pointer_t<decltype(row_ptr)>>;
+            const int k = a.fanout;
+            auto group = [&](auto kern, int rows_per_wave) {
+                hipLaunchKernelGGL(kern, dim3(grid_for(a.rows_bound, (256 / kWave) * rows_per_wave, 16384)), dim3(256),
+                                   0, s, row_ptr, a.col, a.nodes, a.n_prev, a.indptr, a.nbrs, k, key0, key1, a.hop,
+                                   a.eta, a.part_col, a.part_cnt, first, a.map_tag, a.slot_stride, a.n_nodes);
+            };
+            const bool parted = a.part_col && a.part_cnt;
+            if (parted && k > 0 && k <= 8)
+                group(k_sample_biased_group<OffT, 8>, 8);
+            else if (parted && k > 0 && k <= 16)
+                group(k_sample_biased_group<OffT, 16>, 4);
+            else if (parted && k > 0 && k <= 32)
+                group(k_sample_biased_group<OffT, 32>, 2);
+            else
+                hipLaunchKernelGGL(k_sample_biased<OffT>, dim3(grid), dim3(256), 0, s, row_ptr, a.col, a.nodes, a.n_prev,
+                                   a.indptr, a.nbrs, k, key0, key1, a.hop, a.bias_slot_map, a.eta, a.part_col,
+                                   a.part_cnt, first, a.map_tag, a.slot_stride, a.n_nodes);
+        };
         if (a.offsets_i64)
-            hipLaunchKernelGGL(k_sample_biased<int64_t>, dim3(grid), dim3(256), 0, s, (const int64_t *)a.row_ptr, a.col,
-                               a.nodes, a.n_prev, a.indptr, a.nbrs, a.fanout, key0, key1, a.hop, a.bias_slot_map,
-                               a.eta, a.part_col, a.part_cnt, (unsigned long long *)a.first_map, a.map_tag,
-                               a.slot_stride, a.n_nodes);
+            run((const int64_t *)a.row_ptr);
         else
-            hipLaunchKernelGGL(k_sample_biased<int32_t>, dim3(grid), dim3(256), 0, s, (const int32_t *)a.row_ptr, a.col,
-                               a.nodes, a.n_prev, a.indptr, a.nbrs, a.fanout, key0, key1, a.hop, a.bias_slot_map,
-                               a.eta, a.part_col, a.part_cnt, (unsigned long long *)a.first_map, a.map_tag,
-                               a.slot_stride, a.n_nodes);
+            run((const int32_t *)a.row_ptr);
         GNNAV_HIP(hipGetLastError());
         return;
     }
