@@ -417,6 +417,10 @@ __global__ void __launch_bounds__(64 * (kMulWaves + kRowWaves))
         const int32_t n = g * 32 + 8 * q + 4 * h;
         f32x4c s = {1.f, 1.f, 1.f, 1.f};
         if (!redo) s = *(const f32x4c *)(inv + n);
+        // both scales at once: one after the other could leave fp32's range on the way
+        int exp[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) exp[e] = (int)(__float_as_uint(back) >> 23) + (int)(__float_as_uint(s[e]) >> 23) - 254;
 #pragma unroll
         for (int m = 0; m < TM; ++m) {
             const int64_t row = m0 + (wm * TM + m) * 32 + lr;
@@ -424,7 +428,7 @@ __global__ void __launch_bounds__(64 * (kMulWaves + kRowWaves))
             f32x4c v;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                v[e] = acc[m][4 * q + e] * back * s[e];
+                v[e] = ldexpf(acc[m][4 * q + e], exp[e]);
                 if (relu) v[e] = fmaxf(v[e], 0.f);
             }
             float *o = C + row * ldc + n;
