@@ -359,10 +359,15 @@ gnnav_status gnnav_aggregate_mean(const int32_t *indptr_dev, const int32_t *indi
  * for m rows, with W row-major [2*d_in, d_out] (device), self and agg
  * device [m x d_in] with strides ld_self, ld_agg.  act is ReLU when relu is
  * nonzero.  dt = F32: fp32 operands and output, fp32-accurate products: fp32
- * MFMA for few rows, otherwise both operands as two scaled fp16 parts on the
- * fp16 matrix cores (three part products per fp32 product, accumulated in
- * fp32), and tiles whose rows leave fp16's range as three bf16 parts (six
- * products); see gnnav_combine_kernel.  dt = BF16:
+ * MFMA for few rows, otherwise the fp16 or bf16 matrix cores on parts of both
+ * operands, three or six part products per fp32 product, accumulated in fp32
+ * (see gnnav_combine_kernel).  Each product of a row's entry and a weight
+ * (normal numbers) is within 2^-21 of itself, whatever the sizes of the others
+ * around it; the fp32 sums round on top of that.  Values that leave fp16's
+ * range once rows and weight columns are scaled (about 2^29 between the
+ * largest and the smallest of a tile of rows, or of a column of W) are added in
+ * fp32 or send their tile to six products, so the last bits of a row can depend
+ * on the other rows of the call.  dt = BF16:
  * bf16 operands, fp32 accumulation, output bf16 (nearest-even) when
  * out_bf16 is nonzero, else fp32.  The concatenation [self | agg] is never
  * formed.  self and agg rows start 16-byte aligned; out needs only its
@@ -379,9 +384,10 @@ gnnav_status gnnav_combine(const void *self_dev, int64_t ld_self, const void *ag
  * gnnav_combine, gnnav_sage_forward and gnnav_sage_train_step launch:
  * GNNAV_COMBINE_SKINNY: few rows, fp32 or bf16 MFMA as the dtype;
  * GNNAV_COMBINE_RING: bf16 MFMA; GNNAV_COMBINE_SPLIT: fp32 through fp16 or
- * bf16 parts on the matrix cores (gnnav_sage_train_step's hidden layers take
- * the six products of three bf16 parts, all other calls the three of two fp16
- * parts where the range allows).  Host only,
+ * bf16 parts on the matrix cores.  gnnav_sage_train_step's hidden layers take
+ * the six products of three bf16 parts and all other calls the three of two
+ * fp16 parts where the range allows, so the logits of a training step and of
+ * gnnav_sage_forward agree within rounding, not bit for bit.  Host only,
  * no device work; -1 for dt other than F32/BF16 or sizes <= 0.           */
 enum { GNNAV_COMBINE_SKINNY = 0, GNNAV_COMBINE_RING = 1, GNNAV_COMBINE_SPLIT = 2 };
 int32_t gnnav_combine_kernel(int64_t m, int64_t d_out, gnnav_dtype dt);

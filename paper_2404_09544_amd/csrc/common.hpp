@@ -314,8 +314,8 @@ void launch_aggregate_mean(const int32_t *indptr, const int32_t *indices, int64_
 size_t combine_f32_workspace(int64_t d_in, int64_t d_out);
 void launch_split_weights(const float *w, int64_t d_in, int64_t d_out, void *ws, hipStream_t s);
 void launch_combine_f32(const float *self, int64_t ld_self, const float *agg, int64_t ld_agg, int64_t m,
-                        const int32_t *m_dev, int64_t d_in, int64_t d_out, const void *ws, bool relu, float *out,
-                        int64_t ld_out, hipStream_t s);
+                        const int32_t *m_dev, int64_t d_in, const float *w, int64_t d_out, const void *ws, bool relu,
+                        float *out, int64_t ld_out, hipStream_t s);
 
 // combine_stream.hip
 bool combine_streams(int64_t d_in, const void *w, int64_t d_out, bool out_bf16, const void *out, int64_t ld_out);

@@ -792,7 +792,7 @@ static void launch_f32(const float *self, int64_t ld_self, const float *agg, int
     }
     {
         KernelTimer tk(label, s);
-        launch_combine_f32(self, ld_self, agg, ld_agg, m, m_dev, k, n, g_wt.buf.p, relu, out, ld_out, s);
+        launch_combine_f32(self, ld_self, agg, ld_agg, m, m_dev, k, w, n, g_wt.buf.p, relu, out, ld_out, s);
     }
     GNNAV_HIP(hipEventRecord(g_wt.last_use, s));
 }

@@ -1,7 +1,14 @@
-"""The fp32 combine on rows and weights whose sizes lie far apart, each row
-against float64 within TERM_TOL (the operands' parts miss 2^-23 of a value
-each, the fp32 sums of a few hundred terms add about 1e-7), at many rows and at
-few."""
+"""The fp32 combine, term by term: every product of an input and a weight is
+held to fp32's precision whatever the size of its neighbours, so inputs whose
+large entries meet small weights (and the other way round) come out as exact as
+ordinary ones.  Each row against float64 within TERM_TOL, at many rows (fp16
+parts on the matrix cores) and at few (fp32 matrix cores), twice with the same
+bits.
+
+TERM_TOL: a term is off by at most 2^-21 of itself (each operand's two parts
+miss 2^-23 of it, the product left out is below 2^-22 of the term), 4.8e-7 of a
+row's norm if all terms were off in the same direction; the fp32 sums of a few
+hundred terms add about 1e-7, rounding at random.  1e-6 covers both."""
 import numpy as np
 import pytest
 
@@ -12,7 +19,8 @@ from test_gpu_parity import G, say  # noqa: F401  (G is a fixture)
 pytestmark = pytest.mark.gpu
 
 TERM_TOL = 1e-6
-MANY = [(2_600, 130, 256), (6_000, 40, 96), (11_000, 70, 40)]
+# every tile shape: 32, 64 and 96 rows by 256 columns, 64 and 128 by 128
+MANY = [(2_600, 130, 256), (10_500, 70, 200), (20_902, 66, 256), (6_000, 40, 96), (20_000, 48, 128), (11_000, 70, 40)]
 FEW = [(96, 130, 256)]
 
 
@@ -23,7 +31,9 @@ def _inputs(m, d_in, d_out, seed):
 
 
 def _check(G, S, A, Wt, what):
-    got = _combine(G, S, A, Wt, False).astype(np.float64)
+    got = _combine(G, S, A, Wt, False)
+    assert np.array_equal(got, _combine(G, S, A, Wt, False)), f"{what}: two runs differ"
+    got = got.astype(np.float64)
     z = np.concatenate([S, A], axis=1).astype(np.float64) @ Wt.astype(np.float64)
     assert np.isfinite(got).all(), what
     err = np.linalg.norm(got - z, axis=1) / np.linalg.norm(z, axis=1)
@@ -38,3 +48,82 @@ def test_scales_are_undone_without_overflow(G, m, d_in, d_out, x, w):
     say("combine f32 scales", m, d_in, d_out, x, w)
     _, S, A, Wt = _inputs(m, d_in, d_out, m)
     _check(G, S * np.float32(x), A * np.float32(x), Wt * np.float32(w), f"rows {x:g}, weights {w:g}")
+
+
+@pytest.mark.parametrize("m,d_in,d_out", MANY + FEW)
+@pytest.mark.parametrize("half", ["self", "agg", "both"])
+@pytest.mark.parametrize("columns", [1, 5])
+@pytest.mark.parametrize("p", [10, 20, 30, 40])
+def test_raw_columns_with_weights_to_match(G, m, d_in, d_out, half, columns, p):
+    """A few features 2^p times the others, their weights 2^-p times."""
+    say("combine f32 raw columns", m, d_in, d_out, half, columns, p)
+    rng, S, A, Wt = _inputs(m, d_in, d_out, p)
+    for x, w, name in ((S, Wt[:d_in], "self"), (A, Wt[d_in:], "agg")):
+        if half in (name, "both"):
+            k = rng.choice(d_in, columns, replace=False)
+            x[:, k] *= np.float32(2.0 ** p)
+            w[k] *= np.float32(2.0 ** -p)
+    _check(G, S, A, Wt, f"{columns} columns of {half} by 2^{p}")
+
+
+@pytest.mark.parametrize("m,d_in,d_out", MANY + FEW)
+@pytest.mark.parametrize("kind", ["zero_weights", "some_zero_weights", "zero_feature", "tiny_weight", "small_rest"])
+def test_large_entries_that_do_not_count(G, m, d_in, d_out, kind):
+    """Large entries whose partner is zero (or all but): the small rest is the result."""
+    say("combine f32 large entries", m, d_in, d_out, kind)
+    rng, S, A, Wt = _inputs(m, d_in, d_out, 7)
+    k = d_in // 3
+    if kind == "zero_weights":          # a raw column no output reads
+        S[:, k] *= np.float32(2.0 ** 27)
+        Wt[k] = 0
+    elif kind == "some_zero_weights":   # one that half of the outputs read
+        A[:, k] *= np.float32(2.0 ** 30)
+        Wt[d_in + k, ::2] = 0
+        Wt[d_in + k, 1::2] *= np.float32(2.0 ** -30)
+    elif kind == "zero_feature":        # huge weights on a feature that is always zero
+        S[:, k] = 0
+        Wt[k] *= np.float32(2.0 ** 40)
+    elif kind == "tiny_weight":         # the same the other way round
+        S[:, k] *= np.float32(2.0 ** -40)
+        Wt[k] *= np.float32(2.0 ** 40)
+    elif kind == "small_rest":          # one entry of 2^40 in one row that meets a zero weight
+        S[m // 2, k] = np.float32(2.0 ** 40)
+        Wt[k] = 0
+    _check(G, S, A, Wt, kind)
+
+
+@pytest.mark.parametrize("m,d_in,d_out", MANY)
+@pytest.mark.parametrize("count", [1, 32, 33, 500])
+@pytest.mark.parametrize("size", ["small", "large", "both"])
+def test_outliers_of_one_tile(G, m, d_in, d_out, count, size):
+    """Single entries far outside the range of the rows around them, their
+    column's weights scaled to match: `count` of them among 32 rows."""
+    say("combine f32 outliers", m, d_in, d_out, count, size)
+    rng, S, A, Wt = _inputs(m, d_in, d_out, count)
+    small, large = rng.choice(d_in, 2, replace=False)
+    S[:, small] = 0
+    A[:, large] = 0
+    Wt[small] *= np.float32(2.0 ** 45)
+    Wt[d_in + large] *= np.float32(2.0 ** -45)
+    rows = (m // 64) * 32 + np.resize(rng.permutation(32), count)
+    if size != "large":
+        S[rows[::2], small] = np.float32(1.25 * 2.0 ** -45)
+    if size != "small":
+        A[rows[1::2] if count > 1 else rows, large] = np.float32(-1.75 * 2.0 ** 45)
+    _check(G, S, A, Wt, f"{count} {size} outliers")
+
+
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("m,d_in,d_out,ld_extra", [
+    (2_601, 33, 256, 0), (2_688, 63, 250, 1), (10_496, 64, 192, 0), (10_497, 65, 256, 3), (20_929, 127, 255, 0),
+    (24_576, 128, 256, 1), (5_153, 129, 500, 0), (5_120, 192, 128, 0), (5_185, 193, 127, 1), (16_384, 65, 65, 0),
+    (32_768, 40, 100, 0), (32_769, 40, 128, 0)])
+def test_edges(G, m, d_in, d_out, ld_extra, relu):
+    """Rows, widths and columns around a tile, a step and a column group."""
+    say("combine f32 edges", m, d_in, d_out, ld_extra, relu)
+    _, S, A, Wt = _inputs(m, d_in, d_out, m + d_in)
+    z = np.concatenate([S, A], axis=1).astype(np.float64) @ Wt.astype(np.float64)
+    scale = np.linalg.norm(z, axis=1)
+    got = _combine(G, S, A, Wt, relu, ld_extra)
+    err = np.linalg.norm(got - (np.maximum(z, 0) if relu else z), axis=1) / scale
+    assert err.max() <= TERM_TOL, f"row {int(err.argmax())} off by {err.max():.3e}"
