@@ -586,6 +586,25 @@ int64_t f32_kt(int64_t d_in) { return (d_in + kStep - 1) / kStep; }
 int64_t f32_cols(int64_t d_out) { return (d_out + 255) / 256 * 256; }
 }  // namespace
 
+// Where k_combine_f32 beats k_combine_split, measured over d_in 16 .. 602, d_out
+// 32 .. 700 and 2,600 .. 500,000 rows (us, k_combine_split first).  It takes
+// whole groups of 256 columns, one workgroup per compute unit and 64 k a step:
+//   d_in <= 64: 100,000 x 32 x 32 20 against 36, 66,000 x 64 x 384 63 against 71,
+//     at best 20,900 x 64 x 256 25 against 21;
+//   d_out <= 64: 100,000 x 200 x 64 62 against 85, at best 50.6 against 46.4;
+//   d_out <= 128 in one round of tiles (128 rows by 256 units) 1.1 to 1.4 times as
+//     fast, in more rounds 0.8 to 1.1 times unless the rows are long;
+//   d_out in (128, 256]: 1.1 to 1.6 times as fast everywhere (20,902 x 602 x 256 94
+//     against 61, 100,000 x 100 x 256 100 against 89);
+//   d_out > 256: 1.0 to 1.5 times where more than 3/4 of the groups' columns are
+//     used or the rows are long, 0.8 to 1.4 times elsewhere.
+bool combine_f32_parts(int64_t m, int64_t d_in, int64_t d_out) {
+    if (d_in <= 64 || d_out <= 64) return false;
+    const bool long_rows = d_in > 256;
+    if (d_out <= 128) return long_rows || m <= 256 * 128;
+    return d_out <= 256 || long_rows || 4 * d_out > 3 * f32_cols(d_out);
+}
+
 size_t combine_f32_workspace(int64_t d_in, int64_t d_out) {
     const size_t values = (size_t)(f32_cols(d_out) * 2 * f32_kt(d_in) * kStep);
     return values * 2 * 5 + (size_t)f32_cols(d_out) * sizeof(float) + (size_t)f32_cols(d_out) / 8 * sizeof(int32_t);
@@ -632,11 +651,9 @@ void launch_combine_f32(const float *self, int64_t ld_self, const float *agg, in
         if (best == 3) run(i3, i1, i8);
         else if (best == 2) run(i2, i1, i8);
         else run(i1, i1, i8);
-    } else if (d_out > 64) {
+    } else {
         if (cost(2, 4) < cost(4, 4)) run(i1, i2, i4);
         else run(i2, i2, i4);
-    } else {
-        run(i1, i4, i2);
     }
     GNNAV_HIP(hipGetLastError());
 }

@@ -309,8 +309,9 @@ void launch_aggregate_mean(const int32_t *indptr, const int32_t *indices, int64_
                            const int32_t *n_dst_dev, const void *x, int64_t ld_x, int64_t d, bool bf16, void *out,
                            int64_t ld_out, hipStream_t s, const char *label = "aggregate_mean");
 
-// combine_f32.hip: the split weights' workspace, the launch that fills it and
-// the one that reads it
+// combine_f32.hip: whether it takes an fp32 combine of many rows, the split
+// weights' workspace, the launch that fills it and the one that reads it
+bool combine_f32_parts(int64_t m, int64_t d_in, int64_t d_out);
 size_t combine_f32_workspace(int64_t d_in, int64_t d_out);
 void launch_split_weights(const float *w, int64_t d_in, int64_t d_out, void *ws, hipStream_t s);
 void launch_combine_f32(const float *self, int64_t ld_self, const float *agg, int64_t ld_agg, int64_t m,

@@ -884,7 +884,7 @@ void launch_combine(const void *self, int64_t ld_self, const void *agg, int64_t 
         KernelTimer t(label, s);
         launch_combine_stream((const uint16_t *)self, ld_self, (const uint16_t *)agg, ld_agg, m, m_dev, d_in,
                               (const uint16_t *)w, d_out, relu, out_bf16, out, ld_out, s);
-    } else if (!bf16 && !six_products) {
+    } else if (!bf16 && !six_products && combine_f32_parts(m, d_in, d_out)) {
         launch_f32((const float *)self, ld_self, (const float *)agg, ld_agg, m, m_dev, d_in, (const float *)w, d_out, relu,
                    (float *)out, ld_out, s, label);
     } else {

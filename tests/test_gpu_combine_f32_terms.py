@@ -19,8 +19,9 @@ from test_gpu_parity import G, say  # noqa: F401  (G is a fixture)
 pytestmark = pytest.mark.gpu
 
 TERM_TOL = 1e-6
-# every tile shape: 32, 64 and 96 rows by 256 columns, 64 and 128 by 128
-MANY = [(2_600, 130, 256), (10_500, 70, 200), (20_902, 66, 256), (6_000, 40, 96), (20_000, 48, 128), (11_000, 70, 40)]
+# every tile shape: 32, 64 and 96 rows by 256 columns, 64 and 128 by 128; and the
+# six products that narrow calls take
+MANY = [(2_600, 130, 256), (10_500, 70, 200), (20_902, 66, 256), (6_000, 72, 96), (20_000, 80, 128), (11_000, 70, 40)]
 FEW = [(96, 130, 256)]
 
 
@@ -115,9 +116,11 @@ def test_outliers_of_one_tile(G, m, d_in, d_out, count, size):
 
 @pytest.mark.parametrize("relu", [False, True])
 @pytest.mark.parametrize("m,d_in,d_out,ld_extra", [
-    (2_601, 33, 256, 0), (2_688, 63, 250, 1), (10_496, 64, 192, 0), (10_497, 65, 256, 3), (20_929, 127, 255, 0),
+    (2_601, 65, 256, 0), (2_688, 127, 250, 1), (10_496, 128, 192, 0), (10_497, 66, 256, 3), (20_929, 129, 255, 0),
     (24_576, 128, 256, 1), (5_153, 129, 500, 0), (5_120, 192, 128, 0), (5_185, 193, 127, 1), (16_384, 65, 65, 0),
-    (32_768, 40, 100, 0), (32_769, 40, 128, 0)])
+    # either side of where narrow and short rows go to the six products
+    (32_768, 100, 128, 0), (32_769, 100, 128, 0), (40_000, 257, 100, 1), (2_600, 64, 256, 0), (16_384, 100, 64, 0),
+    (9_000, 256, 384, 0), (9_000, 257, 300, 0), (9_000, 100, 385, 3)])
 def test_edges(G, m, d_in, d_out, ld_extra, relu):
     """Rows, widths and columns around a tile, a step and a column group."""
     say("combine f32 edges", m, d_in, d_out, ld_extra, relu)
