@@ -896,6 +896,15 @@ __device__ __forceinline__ uint32_t wave_inclusive_dpp(uint32_t x) {
     return x;
 }
 
+// Whether a thread's kScanItems slots from p0 on all lie in a list of n: by the
+// difference, as n may be any hop bound below 2^31 and the last tile's threads
+// start up to 2^31 - kScanItems.
+__host__ __device__ constexpr bool whole_items(int32_t p0, int32_t n) { return n - p0 >= kScanItems; }
+static_assert(!whole_items(INT32_MAX - 7, INT32_MAX - 63) && !whole_items(INT32_MAX - 7, INT32_MAX - 1) &&
+                  whole_items(INT32_MAX - 15, INT32_MAX - 7) && whole_items(0, 8) && !whole_items(8, 15) &&
+                  !whole_items(2040, 0),
+              "whole and partial items up to the largest list");
+
 // Single-pass scan as k_scan_onepass (tickets, look-back and its bound are
 // shared).  Bound by its chain of dependent memory round trips (row count,
 // ticket, slots, node table, look-back), so each is taken once: a tile's slots
@@ -933,7 +942,7 @@ __global__ void __launch_bounds__(kScanThreads) k_union_slots(UnionArgs u, Side 
         const int32_t p0 = (int32_t)(tile * kScanTile) + (int32_t)threadIdx.x * kScanItems;
 
         int32_t id[kScanItems];
-        if (p0 + kScanItems <= n) {   // p0 is a multiple of 8 and the list 256-byte aligned
+        if (whole_items(p0, n)) {   // p0 is a multiple of 8 and the list 256-byte aligned
             const int4 a = *(const int4 *)(u.slots + p0), b = *(const int4 *)(u.slots + p0 + 4);
             id[0] = a.x, id[1] = a.y, id[2] = a.z, id[3] = a.w;
             id[4] = b.x, id[5] = b.y, id[6] = b.z, id[7] = b.w;

@@ -60,3 +60,28 @@ def test_slot_list_tiles(G, k, rows):
     for fan in ([k], [k, 2], [-1, k] if rows < 100 else [k, -1]):
         G.sample(g, dev(seeds), fan, 21, blk)
         _check(blk, O.sample_blocks(csr, seeds, fan, 21))
+
+
+def test_slot_list_up_to_int32(G):
+    """The largest slot list: 33,554,431 rows of 64 slots, 64 short of 2^31, so
+    that the last tile's last threads start within 8 of 2^31.  A ring whose
+    vertex 0 also points at 100 others (for a maximum degree above 64)."""
+    import torch
+    n = 33_554_431
+    say("slot list up to int32", n)
+    src = np.concatenate([np.arange(n, dtype=np.int32), np.zeros(100, np.int32)])
+    dst = np.concatenate([(np.arange(n, dtype=np.int64) + 1) % n, np.arange(1000, 1100)]).astype(np.int32)
+    g = G.Graph(n, src, dst, symmetrize=False)
+    blk = G.Blocks()
+    seeds = torch.arange(n, dtype=torch.int32, device="cuda")
+    G.sample(g, seeds, [64], 3, blk)
+    nodes, sizes, ip, nb, ix = blk.to_host()
+    assert sizes == [n, n] and np.array_equal(nodes, np.arange(n, dtype=np.int32))
+    deg = np.ones(n, np.int64)
+    deg[0] = 64
+    assert np.array_equal(np.diff(ip[0]), deg) and ip[0][0] == 0
+    assert len(nb[0]) == n + 63 and np.array_equal(nb[0], ix[0])   # every vertex is its own local id
+    assert np.array_equal(nb[0][64:], (np.arange(1, n, dtype=np.int64) + 1) % n)
+    assert set(nb[0][:64].tolist()) <= {1, *range(1000, 1100)} and len(set(nb[0][:64].tolist())) == 64
+    blk.close()
+    g.close()
