@@ -1372,6 +1372,41 @@ static const char *kAggTLabel[] = {"aggregate_mean_t.l1", "aggregate_mean_t.l2",
                                    "aggregate_mean_t.l4+"};
 static const char *kCscLabel[] = {"csc_build.l1", "csc_build.l2", "csc_build.l3", "csc_build.l4+"};
 
+// Strides of a layer's input gradient: self and aggregate part side by side
+// from one product with all of W's rows where that keeps the aggregate part's
+// rows 16-byte aligned (1,024 x 41 x 2 x 256, with the weights' copy: 22.4 us in
+// two, 12.0 in one), else each on its own.
+struct InputGrad {
+    bool both;
+    int64_t ld;
+    explicit InputGrad(int64_t din) : both(din % 4 == 0), ld(both ? 2 * din : padded_ld(din, 4)) {}
+};
+
+// The backward's buffers, each as large as its largest layer needs, before any
+// of the step's work is enqueued: a buffer that grew from one layer to the next
+// would wait for the stream and free and allocate again in mid-step.
+static void reserve_backward(gnnav_blocks *b, const int32_t *dims, int L, hipStream_t s) {
+    const BlockRows br{b};
+    size_t dz[2] = {0, 0}, dself = 0, dagg = 0, part = 0;
+    for (int l = 1; l <= L; ++l) {   // the largest blocks first
+        const int hb = L - l + 1;
+        const int64_t din = dims[l - 1], dout = dims[l], n_dst = br.rows(hb), rows = std::max<int64_t>(n_dst, 1);
+        dz[l & 1] = std::max(dz[l & 1], (size_t)(rows * padded_ld(dout, 4) * 4));
+        part = std::max(part, wgrad_workspace(n_dst, din, dout));
+        if (l == 1) continue;
+        const InputGrad ig(din);
+        dself = std::max(dself, (size_t)(rows * ig.ld * 4));
+        if (!ig.both) dagg = std::max(dagg, (size_t)(rows * ig.ld * 4));
+        b->csc.reserve(br.edges(hb), br.rows(hb + 1), b->scan, s);
+    }
+    for (int k = 0; k < 2; ++k)
+        if (dz[k]) b->dz[k].ensure(dz[k], s);
+    if (dself) b->dself.ensure(dself, s);
+    if (dagg) b->dagg.ensure(dagg, s);
+    b->wpart.ensure(part, s);
+    b->row_loss.ensure(std::max<int64_t>(br.rows(1), 1) * 4, s);
+}
+
 extern "C" gnnav_status gnnav_sage_train_step(gnnav_blocks *b, const float *x_dev, int64_t ld_x, float *const *W_dev,
                                               const int32_t *dims, int32_t n_layers, const int32_t *labels_dev,
                                               float lr, float *logits_dev, int64_t ld_out, float *loss_dev,
@@ -1382,14 +1417,13 @@ extern "C" gnnav_status gnnav_sage_train_step(gnnav_blocks *b, const float *x_de
         GNNAV_CHECK(std::isfinite(lr), GNNAV_E_INVALID, "lr is not finite");
         const int L = n_layers;
         hipStream_t s = (hipStream_t)stream;
+        reserve_backward(b, dims, L, s);
         forward_impl(b, x_dev, ld_x, (const void *const *)W_dev, dims, L, false, logits_dev, ld_out, true, s);
         const BlockRows br{b};
         auto ld4 = [](int64_t d) { return padded_ld(d, 4); };
         // dZ of the last layer: rows F_0
         {
             const int64_t n0 = br.rows(1);
-            b->dz[L & 1].ensure(std::max<int64_t>(n0, 1) * ld4(dims[L]) * 4, s);
-            b->row_loss.ensure(std::max<int64_t>(n0, 1) * 4, s);
             launch_softmax_xent(logits_dev, ld_out, n0, br.rows_dev(1), dims[L], b->nodes.as<int32_t>(), labels_dev,
                                 b->dz[L & 1].as<float>(), ld4(dims[L]), b->row_loss.as<float>(), nullptr, s);
         }
@@ -1406,13 +1440,9 @@ extern "C" gnnav_status gnnav_sage_train_step(gnnav_blocks *b, const float *x_de
             const float *W = W_dev[l - 1];
             if (l > 1) {
                 // gradient of the layer's input: self part and aggregate part
-                // side by side from one product with all of W's rows where that
-                // keeps the aggregate part's rows 16-byte aligned (1,024 x 41 x
-                // 2 x 256, with the weights' copy: 22.4 us in two, 12.0 in one)
-                const bool both = din % 4 == 0;
-                const int64_t ldd = both ? 2 * din : ld4(din);
-                b->dself.ensure(std::max<int64_t>(n_dst, 1) * ldd * 4, s);
-                if (!both) b->dagg.ensure(std::max<int64_t>(n_dst, 1) * ldd * 4, s);
+                const InputGrad ig(din);
+                const bool both = ig.both;
+                const int64_t ldd = ig.ld;
                 float *dself = b->dself.as<float>(), *dagg = both ? dself + din : b->dagg.as<float>();
                 launch_matmul_bt(G, ldg, n_dst, n_dst_dev, dout, W, dout, both ? 2 * din : din, dself, ldd, s,
                                  kBwdGemmLabel[tag]);
@@ -1421,7 +1451,6 @@ extern "C" gnnav_status gnnav_sage_train_step(gnnav_blocks *b, const float *x_de
                                      kBwdGemmLabel[tag]);
                 b->csc.build(b->indptr[hb - 1].as<int32_t>(), b->indices[hb - 1].as<int32_t>(), n_dst, n_dst_dev,
                              br.edges_dev(hb), br.edges(hb), n_src, b->scan, s, kCscLabel[tag]);
-                b->dz[(l - 1) & 1].ensure(std::max<int64_t>(n_src, 1) * ld4(din) * 4, s);
                 launch_aggregate_t(b->csc, b->indptr[hb - 1].as<int32_t>(), n_src, n_src_dev, n_dst, n_dst_dev,
                                    dagg, ldd, dself, ldd, X, ldx, din,
                                    b->dz[(l - 1) & 1].as<float>(), ld4(din), s, kAggTLabel[tag]);

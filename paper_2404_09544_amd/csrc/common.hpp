@@ -253,6 +253,8 @@ struct ScanState;
 struct CscWorkspace {
     DevBuf keys[2], vals[2], hist, offs, col_ptr;
     const int32_t *sorted_rows = nullptr;
+    // the buffers of a build with these bounds
+    void reserve(int64_t e_bound, int64_t n_src_bound, ScanState &scan, hipStream_t s);
     void build(const int32_t *indptr, const int32_t *indices, int64_t n_dst, const int32_t *n_dst_dev,
                const int32_t *n_edges_dev, int64_t e_bound, int64_t n_src_bound, ScanState &scan, hipStream_t s,
                const char *label);
@@ -281,6 +283,7 @@ void launch_aggregate_t(const CscWorkspace &csc, const int32_t *indptr, int64_t 
                         int64_t n_self, const int32_t *n_self_dev, const float *dagg, int64_t ld_dagg,
                         const float *dself, int64_t ld_dself, const float *mask, int64_t ld_mask, int64_t d,
                         float *out, int64_t ld_out, hipStream_t s, const char *label);
+size_t wgrad_workspace(int64_t m, int64_t d_in, int64_t d_out);   // bytes of `part`
 void launch_wgrad(const float *x_self, int64_t ld_self, const float *agg, int64_t ld_agg, int64_t m,
                   const int32_t *m_dev, int64_t d_in, const float *dz, int64_t ld_dz, int64_t d_out, DevBuf &part,
                   float *dw, float *w, float lr, hipStream_t s, const char *label,

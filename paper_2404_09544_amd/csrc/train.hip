@@ -279,6 +279,42 @@ __global__ void __launch_bounds__(256) k_col_ptr(const int32_t *__restrict__ key
     }
 }
 
+namespace {
+// Passes, tiles and their size of a sort of at most `edges` source ids below n_src.
+struct CscPlan {
+    int passes, iters;   // 8-bit digits; elements of a tile per thread
+    int64_t ntiles;
+    bool direct;         // every scatter workgroup adds up all tiles' counts itself
+    CscPlan(int64_t edges, int64_t n_src) {
+        int bits = 1;
+        while (bits < 31 && (int64_t(1) << bits) < n_src) ++bits;
+        passes = (bits + 7) / 8;
+        // the smallest tiles of which there are at most kCscTiles; past that (64
+        // tiles of 2,048) the counts are scanned by launches of their own
+        iters = 1;
+        while (iters < kSortIters && edges > kCscTiles * kSortThreads * iters) iters *= 2;
+        const int64_t tile = (int64_t)kSortThreads * iters;
+        ntiles = (edges + tile - 1) / tile;
+        direct = ntiles <= kCscTiles;
+    }
+};
+}  // namespace
+
+void CscWorkspace::reserve(int64_t e_bound, int64_t n_src_bound, ScanState &scan, hipStream_t s) {
+    const int64_t eb = std::max<int64_t>(e_bound, 1);
+    const CscPlan p(eb, n_src_bound);
+    for (int k = 0; k < 2; ++k) {
+        keys[k].ensure(eb * sizeof(int32_t), s);
+        vals[k].ensure(eb * sizeof(int32_t), s);
+    }
+    hist.ensure((p.direct ? p.passes : 1) * 256 * p.ntiles * sizeof(int32_t), s);
+    if (!p.direct) {
+        offs.ensure(256 * p.ntiles * sizeof(int32_t), s);
+        scan.ensure(256 * p.ntiles, s);
+    }
+    col_ptr.ensure((n_src_bound + 1) * sizeof(int32_t), s);
+}
+
 // Sorted (source, destination row) pairs of one block and its column
 // pointers.  n_edges_dev: device edge count (<= e_bound); n_src_bound sizes
 // the key range; the buffers are grow-only.
@@ -286,26 +322,11 @@ void CscWorkspace::build(const int32_t *indptr, const int32_t *indices, int64_t 
                          const int32_t *n_edges_dev, int64_t e_bound, int64_t n_src_bound, ScanState &scan,
                          hipStream_t s, const char *label) {
     KernelTimer t(label, s);
-    const int64_t eb = std::max<int64_t>(e_bound, 1);
-    int bits = 1;
-    while (bits < 31 && (int64_t(1) << bits) < n_src_bound) ++bits;
-    const int passes = (bits + 7) / 8;
-    // the smallest tiles of which there are at most kCscTiles; past that (64
-    // tiles of 2,048) the counts are scanned by launches of their own
-    int iters = 1;
-    while (iters < kSortIters && eb > kCscTiles * kSortThreads * iters) iters *= 2;
-    const int64_t tile = (int64_t)kSortThreads * iters, ntiles = (eb + tile - 1) / tile;
-    const bool direct = ntiles <= kCscTiles;
-    for (int k = 0; k < 2; ++k) {
-        keys[k].ensure(eb * sizeof(int32_t), s);
-        vals[k].ensure(eb * sizeof(int32_t), s);
-    }
-    hist.ensure((direct ? passes : 1) * 256 * ntiles * sizeof(int32_t), s);
-    if (!direct) {
-        offs.ensure(256 * ntiles * sizeof(int32_t), s);
-        scan.ensure(256 * ntiles, s);
-    }
-    col_ptr.ensure((n_src_bound + 1) * sizeof(int32_t), s);
+    reserve(e_bound, n_src_bound, scan, s);
+    const CscPlan plan(std::max<int64_t>(e_bound, 1), n_src_bound);
+    const int passes = plan.passes, iters = plan.iters;
+    const int64_t ntiles = plan.ntiles;
+    const bool direct = plan.direct;
     // pass 0 reads the block's indices directly; values are destination rows
     const int32_t *kin = indices, *vin = vals[1].as<int32_t>();
     int32_t *h = hist.as<int32_t>();
@@ -624,25 +645,39 @@ __global__ void __launch_bounds__(256) k_wgrad_reduce(const float *__restrict__ 
     }
 }
 
+// 128 x 128 tiles (128 x 64 for outputs at most 64 wide); the row range
+// is split so that at most 512 workgroups run, two per compute unit all
+// at once (rounding up left a few for a second round: 233k layer 1 with
+// 20 tiles ran 520).  A split has at least 64 rows, two steps: with few
+// tiles the launch is as long as one workgroup's chain of steps (1,024 x
+// 2 x 256 x 41, 4 tiles: 13.7 us with at least 256 rows a split, 7.0 so)
+namespace {
+struct WgradPlan {
+    int64_t bo, tiles, splits;
+    WgradPlan(int64_t m, int64_t d_in, int64_t d_out) {
+        const int64_t ba = 128;
+        bo = d_out > 64 ? 128 : 64;
+        tiles = 2 * ((d_in + ba - 1) / ba) * ((d_out + bo - 1) / bo);
+        splits = 512 / tiles;
+        splits = std::min<int64_t>(splits, std::max<int64_t>(1, (m + 63) / 64));
+        splits = std::max<int64_t>(1, std::min<int64_t>(splits, 64));
+    }
+};
+}  // namespace
+
+size_t wgrad_workspace(int64_t m, int64_t d_in, int64_t d_out) {
+    return (size_t)(WgradPlan(m, d_in, d_out).splits * 2 * d_in * d_out) * sizeof(float);
+}
+
 void launch_wgrad(const float *x_self, int64_t ld_self, const float *agg, int64_t ld_agg, int64_t m,
                   const int32_t *m_dev, int64_t d_in, const float *dz, int64_t ld_dz, int64_t d_out, DevBuf &part,
                   float *dw, float *w, float lr, hipStream_t s, const char *label, const LossMean &loss) {
     auto a16 = [](const void *p, int64_t ld) { return (((uintptr_t)p & 15u) == 0) && ld % 4 == 0; };
     if (!(a16(x_self, ld_self) && a16(agg, ld_agg) && a16(dz, ld_dz)))
         fail(GNNAV_E_INVALID, "weight gradient operands need 16-byte aligned rows");
-    // 128 x 128 tiles (128 x 64 for outputs at most 64 wide); the row range
-    // is split so that at most 512 workgroups run, two per compute unit all
-    // at once (rounding up left a few for a second round: 233k layer 1 with
-    // 20 tiles ran 520).  A split has at least 64 rows, two steps: with few
-    // tiles the launch is as long as one workgroup's chain of steps (1,024 x
-    // 2 x 256 x 41, 4 tiles: 13.7 us with at least 256 rows a split, 7.0 so)
-    const int64_t BA = 128, BO = d_out > 64 ? 128 : 64;
-    const int64_t tiles = 2 * ((d_in + BA - 1) / BA) * ((d_out + BO - 1) / BO);
-    int64_t splits = 512 / tiles;
-    splits = std::min<int64_t>(splits, std::max<int64_t>(1, (m + 63) / 64));
-    splits = std::max<int64_t>(1, std::min<int64_t>(splits, 64));
-    const int64_t total = 2 * d_in * d_out;
-    part.ensure((size_t)(splits * total) * sizeof(float), s);
+    const WgradPlan plan(m, d_in, d_out);
+    const int64_t BO = plan.bo, tiles = plan.tiles, splits = plan.splits, total = 2 * d_in * d_out;
+    part.ensure(wgrad_workspace(m, d_in, d_out), s);
     {
         KernelTimer t(label, s);
         if (BO == 128)

@@ -132,7 +132,7 @@ def test_aggregate_mean_backward_many_sources(G):
 # ---------------------------------------------------------- weight grad
 
 # 2 * d_in * d_out not a multiple of 4 takes the reduce's one-element lanes:
-# (1, 3, 41) with one split, (3000, 3, 41) with 12, (40000, 5, 33) with 64.
+# (1, 3, 41) with one split, (3000, 3, 41) with 47, (40000, 5, 33) with 64.
 WGRAD_CASES = [(0, 8, 16), (1, 3, 41), (100, 100, 47), (5000, 602, 256), (20902, 602, 256), (95651, 100, 256),
                (13042, 256, 256), (1024, 256, 41), (777, 130, 70), (3000, 3, 41), (40000, 5, 33)]
 
@@ -335,3 +335,48 @@ def test_train_pipeline_matches_sequential(G):
             assert np.array_equal(host(a), host(b))
         assert float(host(slots[-1].loss)[0]) == seq_losses[-1]
     c.set_link_workgroups(64)
+
+
+@pytest.mark.parametrize("fanouts,dims", [([4, 3], [24, 32, 7]), ([4, 3, 2], [24, 32, 32, 7]), ([4, 3], [24, 30, 7])])
+def test_first_step_allocates_each_buffer_once(G, fanouts, dims):
+    """Over fresh blocks a training step allocates every buffer once, at its
+    largest layer's size, so nothing is freed and allocated again in mid-step;
+    a step that runs out of memory leaves blocks that a later one can use."""
+    import torch
+    n, u, v = graph_case("random-4000-40000-3")
+    g = G.Graph(n, u, v)
+    rng = np.random.default_rng(1)
+    L = len(fanouts)
+    ws = [dev(W.glorot(a, b, "f32", seed=a)) for a, b in zip(dims[:-1], dims[1:])]
+    x = dev(padded(f32(rng.normal(size=(n, dims[0]))), "f32"))
+    labels, seeds = dev(rng.integers(0, dims[-1], n).astype(np.int32)), dev(rng.permutation(n)[:300].astype(np.int32))
+    logits, loss = torch.zeros((300, dims[-1]), device="cuda"), torch.zeros(1, device="cuda")
+    grads = [torch.zeros_like(w) for w in ws]
+
+    def step(blk):
+        G.sage_train_step(blk, x, ws, dims, labels, 0.0, logits, loss, grads)
+        return host(loss).copy(), [host(t).copy() for t in grads]
+
+    def fresh():
+        blk = G.Blocks()
+        G.sample(g, seeds, fanouts, 11, blk)
+        return blk
+    ref_loss, ref = step(fresh())      # the library's shared workspace is there from here on
+    # kept aggregates and hidden rows; two gradients, their split and its parts;
+    # the sort's keys, values, counts and column pointers; weight-gradient
+    # parts and row losses
+    expected = (2 * L - 1) + 2 + (2 if dims[1] % 4 else 1) + 6 + 2
+    for k in range(40):
+        say("train allocations", fanouts, dims, k)
+        blk = fresh()
+        try:
+            G.debug_fail_allocations(k)
+            step(blk)
+            break
+        except G.GnnavError as e:
+            assert e.status == 3, e    # E_NOMEM
+        finally:
+            G.debug_fail_allocations(-1)
+        again_loss, again = step(blk)
+        assert np.array_equal(again_loss, ref_loss) and all(np.array_equal(a, b) for a, b in zip(again, ref))
+    assert k == expected, (k, expected)
