@@ -114,10 +114,7 @@ ErrorWord device_error_word() {
     if (!g_err_word[dev].dev) {
         void *ptr = nullptr, *host = nullptr, *mapped = nullptr;
         GNNAV_HIP(hipGetSymbolAddress(&ptr, HIP_SYMBOL(g_device_errors)));
-        if (hipHostMalloc(&host, sizeof(uint32_t), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
-            (void)hipGetLastError();
-            fail(GNNAV_E_NOMEM, "pinned host allocation of the device error word failed");
-        }
+        host_pinned_alloc(&host, sizeof(uint32_t), hipHostMallocMapped | hipHostMallocCoherent, "device error word");
         *(volatile uint32_t *)host = 0;
         GNNAV_HIP(hipHostGetDevicePointer(&mapped, host, 0));
         g_err_host[dev] = (uint32_t *)host;

@@ -368,3 +368,30 @@ def test_dynamic_repeated_ids_match_oracle(G, policy, d, dtype, r, ring):
         assert np.array_equal(host(counts), ref_counts)
         assert np.array_equal(host(out, dtype)[:, :d].view(np.uint8), ref_rows.view(np.uint8))
         check_cache(c, ref, feats)
+
+
+def test_error_word_allocation_can_fail():
+    """The first handle of a process also allocates the device's error word: as
+    any allocation it fails under the hook with E_NOMEM, and the next call works
+    (a process of its own, as the word is kept)."""
+    import os
+    import subprocess
+    import sys
+    code = """
+import paper_2404_09544_amd as G
+for call in (G.Blocks, G.sync):
+    G.debug_fail_allocations(1 if call is G.Blocks else 0)
+    try:
+        call()
+        print("no failure")
+    except G.GnnavError as e:
+        print(e.status)
+G.debug_fail_allocations(-1)
+G.Blocks()
+G.sync()
+print("ok")
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                       capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr
+    assert r.stdout.split() == [str(E_NOMEM), str(E_NOMEM), "ok"], r.stdout
