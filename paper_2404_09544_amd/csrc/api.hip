@@ -172,6 +172,16 @@ extern "C" gnnav_status gnnav_stream_create(int32_t part, int32_t parts, void **
     });
 }
 
+int gnnav::stream_units(hipStream_t s) {
+    uint32_t mask[8] = {};
+    int units = 0;
+    if (hipExtStreamGetCUMask(s, 8, mask) == hipSuccess)
+        for (uint32_t w : mask) units += __builtin_popcount(w);
+    else
+        (void)hipGetLastError();
+    return units > 0 ? units : 256;
+}
+
 extern "C" gnnav_status gnnav_stream_destroy(void *stream) {
     return guarded([&] {
         if (!stream) return;

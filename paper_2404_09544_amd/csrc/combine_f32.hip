@@ -598,6 +598,8 @@ int64_t f32_cols(int64_t d_out) { return (d_out + 255) / 256 * 256; }
 //     against 61, 100,000 x 100 x 256 100 against 89);
 //   d_out > 256: 1.0 to 1.5 times where more than 3/4 of the groups' columns are
 //     used or the rows are long, 0.8 to 1.4 times elsewhere.
+// (By the whole chip's units on every stream, so that a call's bits do not depend
+// on its stream's share.)
 bool combine_f32_parts(int64_t m, int64_t d_in, int64_t d_out) {
     if (d_in <= 64 || d_out <= 64) return false;
     const bool long_rows = d_in > 256;
@@ -638,11 +640,12 @@ void launch_combine_f32(const float *self, int64_t ld_self, const float *agg, in
     const std::integral_constant<int, 3> i3;
     const std::integral_constant<int, 4> i4;
     const std::integral_constant<int, 8> i8;
-    // rows of 32 on the busiest of 256 compute units (one workgroup each at a
-    // time), half a block's work of overhead a workgroup
+    // rows of 32 on the busiest compute unit (one workgroup each at a time),
+    // half a block's work of overhead a workgroup
+    const int64_t units = stream_units(s);
     auto cost = [&](int blocks, int wn) {
         const int64_t wgs = ((m + 32 * blocks - 1) / (32 * blocks)) * ((d_out + 32 * wn - 1) / (32 * wn));
-        return (wgs + 255) / 256 * (2 * blocks + 1);
+        return (wgs + units - 1) / units * (2 * blocks + 1);
     };
     if (d_out > 128) {
         int best = 3;

@@ -284,10 +284,15 @@ bool combine_streams(int64_t d_in, const void *w, int64_t d_out, bool out_bf16, 
 void launch_combine_stream(const uint16_t *self, int64_t ld_self, const uint16_t *agg, int64_t ld_agg, int64_t m,
                            const int32_t *m_dev, int64_t d_in, const uint16_t *w, int64_t d_out, bool relu,
                            bool out_bf16, void *out, int64_t ld_out, hipStream_t s) {
+    // as many workgroups as units to run on: more would come in a second round
+    // that loads the weights again (on half of the units, one workgroup for each
+    // of the chip's against so: 6,000 x 512 x 256 22.4 -> 14.0 us, 24,000 rows 31.6
+    // -> 22.6, 107,000 x 256 x 256 45 -> 40)
+    const int units = stream_units(s);
     auto run = [&](auto kt_, auto tm_, auto wm_, auto wn_) {
         constexpr int KT = decltype(kt_)::value, TM = decltype(tm_)::value, WM = decltype(wm_)::value,
                       WN = decltype(wn_)::value, BM = 32 * TM * WM;
-        const dim3 grid((unsigned)std::min<int64_t>((m + BM - 1) / BM, 256), (unsigned)((d_out + 32 * WN - 1) / (32 * WN)));
+        const dim3 grid((unsigned)std::min<int64_t>((m + BM - 1) / BM, units), (unsigned)((d_out + 32 * WN - 1) / (32 * WN)));
         auto go = [&](auto kern, auto *o) {
             hipLaunchKernelGGL(kern, grid, dim3(64 * WM * WN), 0, s, self, ld_self, agg, ld_agg, m, m_dev, (int32_t)d_in, w,
                                (int32_t)d_out, (int)relu, o, ld_out);

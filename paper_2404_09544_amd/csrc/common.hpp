@@ -81,6 +81,10 @@ struct KernelTimer {
     hipStream_t stream;
 };
 
+// Compute units that work on `s` may run on: all of the device's, or the share
+// of a stream made with a mask (some 0.3 us of host time).
+int stream_units(hipStream_t s);
+
 inline unsigned grid_for(int64_t items, int64_t per_block, int64_t cap) {
     int64_t g = (items + per_block - 1) / per_block;
     if (g > cap) g = cap;

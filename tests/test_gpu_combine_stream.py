@@ -42,3 +42,25 @@ def test_combine_stream_edges(G, m, d_in, d_out, out_bf16):
     if out_bf16:
         z = O.round_bf16_array(np.maximum(z, 0))
     assert_rows_close(O.to_f64(got[:m, :d_out], "bf16" if out_bf16 else "f32"), z, BF16_TOL, "combine stream")
+
+
+@pytest.mark.parametrize("dtype,m,d_in,d_out", [("bf16", 6_000, 256, 256), ("bf16", 40_000, 60, 96), ("f32", 13_720, 70, 256),
+                                                ("f32", 30_000, 80, 128)])
+def test_combine_on_a_share_of_the_units(G, dtype, m, d_in, d_out):
+    """A stream that holds a share of the compute units gets grids of that
+    share; the bits are those of the whole chip."""
+    import torch
+    say("combine share", dtype, m, d_in, d_out)
+    S, A = W.features(m, d_in, dtype, seed=1), W.features(m, d_in, dtype, seed=2)
+    ops = dev(padded(S, dtype)), dev(padded(A, dtype)), dev(W.glorot(d_in, d_out, dtype, seed=3))
+    outs = []
+    for share in (None, (0, 2), (1, 3)):
+        out = torch.zeros((m, d_out), dtype=torch.int16 if dtype == "bf16" else torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        st = G.stream_create(*share) if share else torch.cuda.current_stream()
+        G.combine(ops[0], ops[1], m, d_in, ops[2], d_out, dtype, True, dtype == "bf16", out, stream=st)
+        torch.cuda.synchronize()
+        if share:
+            G.stream_destroy(st)
+        outs.append(host(out, dtype))
+    assert outs[0].any() and all(np.array_equal(outs[0], o) for o in outs[1:])
