@@ -6,12 +6,17 @@
 // in registers.  The group stages up to G neighbour ids in registers (one
 // per lane) and broadcasts them with lane shuffles; neighbour rows are
 // summed in CSR order, eight rows in flight at a time where a lane owns one
-// unit and four where it owns several, and the last few of a destination row
+// unit and four where it owns several, then four, then the last one to three
 // together: sampled rows are short, and one load at a time there made a narrow
-// row's aggregation a chain of memory round trips (a fan-out of 10 took four,
-// it takes two).  Three bf16 layers over fan-outs 15, 10 and 5 of 4,096 seeds
-// 112.5 -> 106 us, a 10,000-vertex batch 82 -> 79; wide rows, bound by sources
-// fetched into L2 again for each edge, 79.9 -> 79.1 (20,827 x 602, fan-out 10).
+// row's aggregation a chain of memory round trips.  All addresses of a group of
+// rows are formed before its first load (formed one by one, each load waited
+// for its own shuffle; seven masked loads for the rest, as before, cost short
+// rows more than they saved).  Measured over 288 shapes of 2 to 40 neighbours,
+// 16 to 602 columns and 300 to 100,000 rows: 1.07 times as fast as four rows in
+// flight and single ones after them, worst 0.91 (300 x 256 of 40 neighbours
+// 6.4 -> 5.3 us, 4,000 x 64 bf16 of 25 7.3 -> 6.4, 4,000 x 128 of 15 5.5 -> 5.1).  Wide
+// rows are bound by sources fetched into L2 again for each edge (20,827 x 602,
+// fan-out 10: 79 us either way).
 // Rows wider than G*Q units are done in column slabs.
 #include "common.hpp"
 
@@ -86,36 +91,56 @@ __global__ void __launch_bounds__(256) k_spmm_mean(const int32_t *__restrict__ i
                 const int nb = min(G, e - p0);
                 int j = 0;
                 for (; j + F <= nb; j += F) {
+                    const uint4 *src[F];
+#pragma unroll
+                    for (int u = 0; u < F; ++u) src[u] = x + (int64_t)__shfl(mine, j + u, G) * x_ld16 + slab + c0;
                     uint4 v[F][Q];
 #pragma unroll
-                    for (int u = 0; u < F; ++u) {
-                        const uint4 *src = x + (int64_t)__shfl(mine, j + u, G) * x_ld16 + slab + c0;
+                    for (int q = 0; q < Q; ++q)
+                        if (live[q])
 #pragma unroll
-                        for (int q = 0; q < Q; ++q)
-                            if (live[q]) v[u][q] = src[q * G];
-                    }
+                            for (int u = 0; u < F; ++u) v[u][q] = src[u][q * G];
 #pragma unroll
-                    for (int u = 0; u < F; ++u)
+                    for (int q = 0; q < Q; ++q)
+                        if (live[q])
 #pragma unroll
-                        for (int q = 0; q < Q; ++q)
-                            if (live[q]) U::add(acc[q], v[u][q]);
+                            for (int u = 0; u < F; ++u) U::add(acc[q], v[u][q]);
+                }
+                if (F == 8 && j + 4 <= nb) {
+                    const uint4 *src[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) src[u] = x + (int64_t)__shfl(mine, j + u, G) * x_ld16 + slab + c0;
+                    uint4 v[4][Q];
+#pragma unroll
+                    for (int q = 0; q < Q; ++q)
+                        if (live[q])
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) v[u][q] = src[u][q * G];
+#pragma unroll
+                    for (int q = 0; q < Q; ++q)
+                        if (live[q])
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) U::add(acc[q], v[u][q]);
+                    j += 4;
                 }
                 if (j < nb) {   // the last few, in flight together too
-                    uint4 v[F - 1][Q];
+                    const uint4 *src[3];
 #pragma unroll
-                    for (int u = 0; u < F - 1; ++u) {
-                        // (past the last one: shuffled from the last, neither read nor added)
-                        const int ju = j + u < nb ? j + u : nb - 1;
-                        const uint4 *src = x + (int64_t)__shfl(mine, ju, G) * x_ld16 + slab + c0;
+                    for (int u = 0; u < 3; ++u)   // (past the last one: shuffled from the last, neither read nor added)
+                        src[u] = x + (int64_t)__shfl(mine, min(j + u, nb - 1), G) * x_ld16 + slab + c0;
+                    uint4 v[3][Q];
 #pragma unroll
-                        for (int q = 0; q < Q; ++q)
-                            if (live[q] && j + u < nb) v[u][q] = src[q * G];
-                    }
+                    for (int q = 0; q < Q; ++q)
+                        if (live[q])
 #pragma unroll
-                    for (int u = 0; u < F - 1; ++u)
+                            for (int u = 0; u < 3; ++u)
+                                if (j + u < nb) v[u][q] = src[u][q * G];
 #pragma unroll
-                        for (int q = 0; q < Q; ++q)
-                            if (live[q] && j + u < nb) U::add(acc[q], v[u][q]);
+                    for (int q = 0; q < Q; ++q)
+                        if (live[q])
+#pragma unroll
+                            for (int u = 0; u < 3; ++u)
+                                if (j + u < nb) U::add(acc[q], v[u][q]);
                 }
             }
 #pragma unroll
