@@ -273,12 +273,35 @@ __global__ void __launch_bounds__(64 * WM * WN) k_combine_stream(const uint16_t 
 }  // namespace
 
 // Whether the streaming kernel takes a bf16 combine of many rows: the weights
-// of 32 columns fit 128 registers (d_in <= 256), and weight and output rows
-// move 16 bytes at a time.  Faster than the ring at every size measured where
-// it applies, from 1,600 x 400 x 256 (9.2 -> 8.3 us) to 400,000 rows.
-bool combine_streams(int64_t d_in, const void *w, int64_t d_out, bool out_bf16, const void *out, int64_t ld_out) {
-    return d_in <= 256 && d_out % 8 == 0 && ld_out % (out_bf16 ? 8 : 4) == 0 &&
-           (((uintptr_t)w | (uintptr_t)out) & 15u) == 0 && ld_out < (1 << 20) && d_out < (1 << 20);
+// of 32 columns fit 128 registers (d_in <= 256), weight and output rows move 16
+// bytes at a time, and it is the faster one.  Ratios are the ring's time over its
+// own, measured over d_in 8 .. 256, d_out 8 .. 768 and 2,600 .. 300,000 rows:
+//   d_out in (128, 256]: 1.0 to 2.4 everywhere;
+//   d_out in (64, 128]: 1.1 to 2.1; 0.7 to 0.95 past 32,768 rows where d_in > 128
+//     is no multiple of 16 (every tile's last chunks are then masked in LDS);
+//   d_out <= 64 has two or four wavefronts to a workgroup: d_in <= 128 1.1 to 1.9, not
+//     a multiple of 16 below 1 past 65,536 rows (0.7 at 300,000 x 40); d_in in
+//     (128, 256) 1.3 to 1.5 up to 16,384 rows, 0.7 at 300,000, and 0.3 to 0.95 where
+//     it is no multiple of 16; d_in = 256 (no bound in the loop) 1.06 to 1.8;
+//   d_out > 256 reads the rows again for every 256 columns: d_in <= 128 1.1 to 2.1,
+//     fp32 results 0.8 to 1.3 unless there are few rows or d_in is small; d_in > 128
+//     1.2 to 1.7 up to 4,096 rows of two groups, 0.6 to 1.2 above, 1.0 to 1.7 from
+//     200,000.
+bool combine_streams(int64_t m, int64_t d_in, const void *w, int64_t d_out, bool out_bf16, const void *out,
+                     int64_t ld_out) {
+    if (!(d_in <= 256 && d_out % 8 == 0 && ld_out % (out_bf16 ? 8 : 4) == 0 &&
+          (((uintptr_t)w | (uintptr_t)out) & 15u) == 0 && ld_out < (1 << 20) && d_out < (1 << 20)))
+        return false;
+    const bool ragged = d_in % 16 != 0, deep = d_in > 128;
+    if (d_out > 256) {
+        const int64_t groups = (d_out + 255) / 256;
+        if (deep) return m * groups <= 8192 || m >= 200000;
+        return out_bf16 || d_in <= 48 || m <= 8192;
+    }
+    if (d_out > 128) return true;
+    if (d_out > 64) return !(deep && ragged) || m <= 32768;
+    if (deep) return d_in == 256 || (!ragged && m <= 16384);
+    return !ragged || m <= 65536;
 }
 
 void launch_combine_stream(const uint16_t *self, int64_t ld_self, const uint16_t *agg, int64_t ld_agg, int64_t m,

@@ -326,7 +326,8 @@ void launch_combine_f32(const float *self, int64_t ld_self, const float *agg, in
                         float *out, int64_t ld_out, hipStream_t s);
 
 // combine_stream.hip
-bool combine_streams(int64_t d_in, const void *w, int64_t d_out, bool out_bf16, const void *out, int64_t ld_out);
+bool combine_streams(int64_t m, int64_t d_in, const void *w, int64_t d_out, bool out_bf16, const void *out,
+                     int64_t ld_out);
 void launch_combine_stream(const uint16_t *self, int64_t ld_self, const uint16_t *agg, int64_t ld_agg, int64_t m,
                            const int32_t *m_dev, int64_t d_in, const uint16_t *w, int64_t d_out, bool relu,
                            bool out_bf16, void *out, int64_t ld_out, hipStream_t s);

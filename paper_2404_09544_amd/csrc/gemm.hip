@@ -11,7 +11,8 @@
 // fp32 accumulation; the skinny fp32 kernel v_mfma_f32_16x16x4_f32.
 //
 // bf16 combines of many rows with d_in <= 256 and aligned outputs run the
-// streaming kernel of combine_stream.hip instead of the ring.
+// streaming kernel of combine_stream.hip instead of the ring where it is the
+// faster one.
 //
 // Ring kernel (rows 16-byte aligned; fp32 and bf16): a 256-thread
 // workgroup owns a BM x BN output tile as WM x (4 / WM) wavefronts.  Both
@@ -880,7 +881,7 @@ void launch_combine(const void *self, int64_t ld_self, const void *agg, int64_t 
             run(std::integral_constant<int, 16>{});
         else
             run(std::integral_constant<int, 8>{});
-    } else if (bf16 && combine_streams(d_in, w, d_out, out_bf16, out, ld_out)) {
+    } else if (bf16 && combine_streams(m, d_in, w, d_out, out_bf16, out, ld_out)) {
         KernelTimer t(label, s);
         launch_combine_stream((const uint16_t *)self, ld_self, (const uint16_t *)agg, ld_agg, m, m_dev, d_in,
                               (const uint16_t *)w, d_out, relu, out_bf16, out, ld_out, s);

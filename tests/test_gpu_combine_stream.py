@@ -17,7 +17,10 @@ pytestmark = pytest.mark.gpu
 CASES = [(10_240, 1, 8), (10_241, 8, 16), (10_303, 15, 32), (10_304, 16, 40), (10_305, 17, 64), (5_121, 100, 72),
          (5_152, 112, 128), (3_649, 128, 136), (2_561, 127, 200), (2_561, 128, 256), (16_384, 128, 256),
          (16_385, 128, 256), (8_193, 129, 256), (8_192, 256, 256), (2_593, 250, 248), (10_272, 200, 48),
-         (5_153, 256, 96), (2_600, 96, 264), (33_000, 128, 64), (16_448, 257, 64)]
+         (5_153, 256, 96), (2_600, 96, 264), (33_000, 128, 64), (16_448, 257, 64),
+         # either side of where the ring takes over again
+         (32_768, 130, 72), (32_769, 130, 72), (16_384, 144, 16), (16_385, 144, 16), (10_240, 200, 64), (65_536, 40, 8),
+         (65_537, 40, 8), (8_192, 100, 264), (8_193, 100, 264), (4_096, 160, 512), (4_097, 160, 512)]
 
 
 @pytest.mark.parametrize("out_bf16", [True, False])
