@@ -648,9 +648,12 @@ __global__ void __launch_bounds__(256) k_wgrad_reduce(const float *__restrict__ 
 // 128 x 128 tiles (128 x 64 for outputs at most 64 wide); the row range
 // is split so that at most 512 workgroups run, two per compute unit all
 // at once (rounding up left a few for a second round: 233k layer 1 with
-// 20 tiles ran 520).  A split has at least 64 rows, two steps: with few
-// tiles the launch is as long as one workgroup's chain of steps (1,024 x
-// 2 x 256 x 41, 4 tiles: 13.7 us with at least 256 rows a split, 7.0 so)
+// 20 tiles ran 520).  A split has at least 256 rows, or 64, two steps, while
+// there are fewer workgroups than units: with few tiles the launch is as long
+// as one workgroup's chain of steps (1,024 x 2 x 256 x 41, 4 tiles: 13.7 us with
+// at least 256 rows a split, 7.0 so), but past one workgroup per unit finer
+// splits only add partial sums to write and read back (5,000 x 2 x 602 x 128: 27
+// us, 31 with 64 rows a split).
 namespace {
 struct WgradPlan {
     int64_t bo, tiles, splits;
@@ -659,7 +662,7 @@ struct WgradPlan {
         bo = d_out > 64 ? 128 : 64;
         tiles = 2 * ((d_in + ba - 1) / ba) * ((d_out + bo - 1) / bo);
         splits = 512 / tiles;
-        splits = std::min<int64_t>(splits, std::max<int64_t>(1, (m + 63) / 64));
+        splits = std::min<int64_t>(splits, std::max<int64_t>((m + 255) / 256, std::min<int64_t>((m + 63) / 64, 256 / tiles)));
         splits = std::max<int64_t>(1, std::min<int64_t>(splits, 64));
     }
 };
