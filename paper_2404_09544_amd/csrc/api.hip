@@ -777,7 +777,7 @@ struct gnnav_blocks {
     DevBuf agg, hid[2];             // forward workspace
     // training: activations kept per layer, gradients, transposed blocks
     DevBuf act_agg[kMaxHops], act_h[kMaxHops];
-    DevBuf dz[2], dself, dagg, wpart, row_loss, dw_tmp;
+    DevBuf bwd;                     // the backward's buffers, see BackwardBuffers
     CscWorkspace csc;
 };
 
@@ -819,7 +819,7 @@ extern "C" void gnnav_blocks_free(gnnav_blocks *b) {
         b->act_agg[h].release();
         b->act_h[h].release();
     }
-    for (DevBuf *d : {&b->dz[0], &b->dz[1], &b->dself, &b->dagg, &b->wpart, &b->row_loss, &b->dw_tmp}) d->release();
+    b->bwd.release();
     b->csc.release();
     if (b->sizes_host) (void)hipHostFree(b->sizes_host);
     delete b;
@@ -1389,30 +1389,46 @@ struct InputGrad {
     explicit InputGrad(int64_t din) : both(din % 4 == 0), ld(both ? 2 * din : padded_ld(din, 4)) {}
 };
 
-// The backward's buffers, each as large as its largest layer needs, before any
-// of the step's work is enqueued: a buffer that grew from one layer to the next
-// would wait for the stream and free and allocate again in mid-step.
-static void reserve_backward(gnnav_blocks *b, const int32_t *dims, int L, hipStream_t s) {
-    const BlockRows br{b};
-    size_t dz[2] = {0, 0}, dself = 0, dagg = 0, part = 0;
-    for (int l = 1; l <= L; ++l) {   // the largest blocks first
-        const int hb = L - l + 1;
-        const int64_t din = dims[l - 1], dout = dims[l], n_dst = br.rows(hb), rows = std::max<int64_t>(n_dst, 1);
-        dz[l & 1] = std::max(dz[l & 1], (size_t)(rows * padded_ld(dout, 4) * 4));
-        part = std::max(part, wgrad_workspace(n_dst, din, dout));
-        if (l == 1) continue;
-        const InputGrad ig(din);
-        dself = std::max(dself, (size_t)(rows * ig.ld * 4));
-        if (!ig.both) dagg = std::max(dagg, (size_t)(rows * ig.ld * 4));
-        b->csc.reserve(br.edges(hb), br.rows(hb + 1), b->scan, s);
+// The backward's buffers, each as large as its largest layer needs, side by side
+// in one allocation made before any of the step's work is enqueued: a buffer
+// that grew from one layer to the next would wait for the stream and free and
+// allocate again in mid-step, and an allocation of 2 MB or more can take 0.3 ms.
+struct BackwardBuffers {
+    float *dz[2] = {nullptr, nullptr};   // gradient of layer l's output in dz[l & 1]
+    float *dself = nullptr, *dagg = nullptr, *row_loss = nullptr;
+    DevBuf part;                         // a view: weight-gradient partials
+    BackwardBuffers(gnnav_blocks *b, const int32_t *dims, int L, hipStream_t s) {
+        const BlockRows br{b};
+        size_t z[2] = {0, 0}, self = 0, agg = 0, parts = 0;
+        for (int l = 1; l <= L; ++l) {   // the largest blocks first
+            const int hb = L - l + 1;
+            const int64_t din = dims[l - 1], dout = dims[l], n_dst = br.rows(hb), rows = std::max<int64_t>(n_dst, 1);
+            z[l & 1] = std::max(z[l & 1], (size_t)(rows * padded_ld(dout, 4) * 4));
+            parts = std::max(parts, wgrad_workspace(n_dst, din, dout));
+            if (l == 1) continue;
+            const InputGrad ig(din);
+            self = std::max(self, (size_t)(rows * ig.ld * 4));
+            if (!ig.both) agg = std::max(agg, (size_t)(rows * ig.ld * 4));
+            b->csc.reserve(br.edges(hb), br.rows(hb + 1), b->scan, s);
+        }
+        const size_t loss = (size_t)std::max<int64_t>(br.rows(1), 1) * 4;
+        auto whole = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
+        b->bwd.ensure(whole(z[0]) + whole(z[1]) + whole(self) + whole(agg) + whole(parts) + whole(loss), s);
+        char *at = b->bwd.as<char>();
+        auto take = [&](size_t bytes) {
+            char *p = at;
+            at += whole(bytes);
+            return bytes ? (float *)p : nullptr;
+        };
+        dz[0] = take(z[0]);
+        dz[1] = take(z[1]);
+        dself = take(self);
+        dagg = take(agg);
+        row_loss = take(loss);
+        part.p = take(parts);
+        part.bytes = parts;
     }
-    for (int k = 0; k < 2; ++k)
-        if (dz[k]) b->dz[k].ensure(dz[k], s);
-    if (dself) b->dself.ensure(dself, s);
-    if (dagg) b->dagg.ensure(dagg, s);
-    b->wpart.ensure(part, s);
-    b->row_loss.ensure(std::max<int64_t>(br.rows(1), 1) * 4, s);
-}
+};
 
 extern "C" gnnav_status gnnav_sage_train_step(gnnav_blocks *b, const float *x_dev, int64_t ld_x, float *const *W_dev,
                                               const int32_t *dims, int32_t n_layers, const int32_t *labels_dev,
@@ -1424,7 +1440,7 @@ extern "C" gnnav_status gnnav_sage_train_step(gnnav_blocks *b, const float *x_de
         GNNAV_CHECK(std::isfinite(lr), GNNAV_E_INVALID, "lr is not finite");
         const int L = n_layers;
         hipStream_t s = (hipStream_t)stream;
-        reserve_backward(b, dims, L, s);
+        BackwardBuffers bw(b, dims, L, s);
         forward_impl(b, x_dev, ld_x, (const void *const *)W_dev, dims, L, false, logits_dev, ld_out, true, s);
         const BlockRows br{b};
         auto ld4 = [](int64_t d) { return padded_ld(d, 4); };
@@ -1432,7 +1448,7 @@ extern "C" gnnav_status gnnav_sage_train_step(gnnav_blocks *b, const float *x_de
         {
             const int64_t n0 = br.rows(1);
             launch_softmax_xent(logits_dev, ld_out, n0, br.rows_dev(1), dims[L], b->nodes.as<int32_t>(), labels_dev,
-                                b->dz[L & 1].as<float>(), ld4(dims[L]), b->row_loss.as<float>(), nullptr, s);
+                                bw.dz[L & 1], ld4(dims[L]), bw.row_loss, nullptr, s);
         }
         for (int l = L; l >= 1; --l) {
             const int tag = l < 4 ? l - 1 : 3;
@@ -1442,7 +1458,7 @@ extern "C" gnnav_status gnnav_sage_train_step(gnnav_blocks *b, const float *x_de
             const int64_t din = dims[l - 1], dout = dims[l];
             const float *X = l == 1 ? x_dev : b->act_h[l - 2].as<float>();
             const int64_t ldx = l == 1 ? ld_x : ld4(din);
-            const float *G = b->dz[l & 1].as<float>();
+            const float *G = bw.dz[l & 1];
             const int64_t ldg = ld4(dout);
             const float *W = W_dev[l - 1];
             if (l > 1) {
@@ -1450,7 +1466,7 @@ extern "C" gnnav_status gnnav_sage_train_step(gnnav_blocks *b, const float *x_de
                 const InputGrad ig(din);
                 const bool both = ig.both;
                 const int64_t ldd = ig.ld;
-                float *dself = b->dself.as<float>(), *dagg = both ? dself + din : b->dagg.as<float>();
+                float *dself = bw.dself, *dagg = both ? dself + din : bw.dagg;
                 launch_matmul_bt(G, ldg, n_dst, n_dst_dev, dout, W, dout, both ? 2 * din : din, dself, ldd, s,
                                  kBwdGemmLabel[tag]);
                 if (!both)
@@ -1460,12 +1476,12 @@ extern "C" gnnav_status gnnav_sage_train_step(gnnav_blocks *b, const float *x_de
                              br.edges_dev(hb), br.edges(hb), n_src, b->scan, s, kCscLabel[tag]);
                 launch_aggregate_t(b->csc, b->indptr[hb - 1].as<int32_t>(), n_src, n_src_dev, n_dst, n_dst_dev,
                                    dagg, ldd, dself, ldd, X, ldx, din,
-                                   b->dz[(l - 1) & 1].as<float>(), ld4(din), s, kAggTLabel[tag]);
+                                   bw.dz[(l - 1) & 1], ld4(din), s, kAggTLabel[tag]);
             }
             // dW_l = [X[0:n_dst] | agg]^T dZ_l, then W_l -= lr * dW_l
             launch_wgrad(X, ldx, b->act_agg[l - 1].as<float>(), ld4(din), n_dst, n_dst_dev, din, G, ldg, dout,
-                         b->wpart, dW_dev ? dW_dev[l - 1] : nullptr, W_dev[l - 1], lr, s, kWgradLabel[tag],
-                         l == L ? LossMean{b->row_loss.as<float>(), br.rows(1), br.rows_dev(1), loss_dev} : LossMean());
+                         bw.part, dW_dev ? dW_dev[l - 1] : nullptr, W_dev[l - 1], lr, s, kWgradLabel[tag],
+                         l == L ? LossMean{bw.row_loss, br.rows(1), br.rows_dev(1), loss_dev} : LossMean());
         }
     });
 }

@@ -362,10 +362,9 @@ def test_first_step_allocates_each_buffer_once(G, fanouts, dims):
         G.sample(g, seeds, fanouts, 11, blk)
         return blk
     ref_loss, ref = step(fresh())      # the library's shared workspace is there from here on
-    # kept aggregates and hidden rows; two gradients, their split and its parts;
-    # the sort's keys, values, counts and column pointers; weight-gradient
-    # parts and row losses
-    expected = (2 * L - 1) + 2 + (2 if dims[1] % 4 else 1) + 6 + 2
+    # kept aggregates and hidden rows; the sort's keys, values, counts and column
+    # pointers; gradients, weight-gradient parts and row losses in one
+    expected = (2 * L - 1) + 6 + 1
     for k in range(40):
         say("train allocations", fanouts, dims, k)
         blk = fresh()
