@@ -4,8 +4,8 @@
 // computations", ARITH 2019).  x = x1 + x2 + x3 + e with |e| < 2^-23 |x|:
 // x1 is the top 16 bits of x (truncation), x2 those of x - x1, x3 those of
 // x - x1 - x2; both differences are exact in fp32.  A product a b then takes
-// the six part products a1 b1, a1 b2, a2 b1, a1 b3, a3 b1, a2 b2; the three
-// it drops are below 2^-30 |a b|.  Part products are exact in fp32.
+// the six part products a1 b1, a1 b2, a2 b1, a1 b3, a3 b1, a2 b2; of the three
+// it drops a2 b3 and a3 b2 are below 2^-22 |a b|.  Part products are exact in fp32.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cstdint>

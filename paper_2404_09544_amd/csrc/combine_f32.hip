@@ -39,12 +39,12 @@
 // time.
 //
 // Measured (us, with the weights' launch; k_combine_split with its own):
-// 20,902 x 1,204 x 256 97 -> 65, 10,400 rows 72 -> 44, 66,000 x 400 x 256 114 ->
-// 85, 107,000 x 256 x 256 100 -> 91, 6,761 x 512 x 256 27.5 -> 19.8.  What is
-// left at 20,902 rows: the products alone, without loads, take 45 us at the
-// clock the matrix cores hold; rows add 10 us, the weights' launch 6.  Data
-// that needs the list (one column 2^10 times the rest) 69, tiles that all take
-// six products (2^20 and more) 92, 66,000 x 400 x 256 134 (113).
+// 20,902 x 1,204 x 256 97 -> 60, 13,720 rows 73 -> 44, 66,000 x 400 x 256 114 -> 81,
+// 107,000 x 256 x 256 100 -> 88, 6,761 x 512 x 256 27.5 -> 18.7.  What is left at
+// 20,902 rows: the products alone, without loads, take 45 us at the clock the
+// matrix cores hold; the weights' launch 6.  Data that needs the list (one column
+// 2^10 times the rest) 64, tiles that all take six products (2^20 and more) 94,
+// 66,000 x 400 x 256 134 (113).
 #include <algorithm>
 #include <type_traits>
 
@@ -205,23 +205,53 @@ struct Outlier {
     float x;
 };
 
+// LDS of a workgroup with tiles of BM rows.
+template <int BM>
+struct F32Shared {
+    u32x4c stages[9 * BM * 8];   // three stages of two planes (six products: of three)
+    float max[kRowWaves];
+    Outlier list[kListMax];
+    int count;     // outliers met so far
+    int over[3];   // too many: [2] before the first step, [t & 1] in step t, read after its barrier
+};
+
+struct F32Args {
+    const float *A0;
+    int64_t lda0;
+    const float *A1;
+    int64_t lda1;
+    int64_t M;
+    const int32_t *m_dev;
+    int32_t K, kt;
+    const float *W;
+    const u32x4c *half_planes, *bf_planes;
+    const float *inv;
+    const int32_t *outside;
+    int32_t N;
+    int relu, vec;
+    float *C;
+    int64_t ldc;
+};
+
+// One workgroup's tile: rows from blockIdx.x * 32 TM WM on, of M.
 template <int TM, int WM, int WN>
-__global__ void __launch_bounds__(64 * (kMulWaves + kRowWaves))
-    k_combine_f32(const float *__restrict__ A0, int64_t lda0, const float *__restrict__ A1, int64_t lda1, int64_t M,
-                  const int32_t *__restrict__ m_dev, int32_t K, int32_t kt, const float *__restrict__ W,
-                  const u32x4c *__restrict__ half_planes, const u32x4c *__restrict__ bf_planes,
-                  const float *__restrict__ inv, const int32_t *__restrict__ outside, int32_t N, int relu, int vec,
-                  float *__restrict__ C, int64_t ldc) {
+__device__ __forceinline__ void combine_f32_tile(const F32Args &a, int64_t M, F32Shared<32 * TM * WM> &sh) {
     static_assert(WM * WN == kMulWaves, "wavefront grid");
     constexpr int BM = 32 * TM * WM, AJ = BM / 16;   // a row thread loads AJ float4 of a step
     constexpr int PL = BM * 8;                       // 16-byte chunks of one plane of a stage
-    __shared__ u32x4c S[9 * PL];                     // three stages of two planes (six products: of three)
-    __shared__ float s_max[kRowWaves];
-    __shared__ Outlier s_list[kListMax];
-    __shared__ int s_count;     // outliers met so far
-    __shared__ int s_over[3];   // too many: [2] before the first step, [t & 1] in step t, read after its barrier
+    const float *__restrict__ A0 = a.A0, *__restrict__ A1 = a.A1, *__restrict__ W = a.W, *__restrict__ inv = a.inv;
+    const u32x4c *__restrict__ half_planes = a.half_planes, *__restrict__ bf_planes = a.bf_planes;
+    const int32_t *__restrict__ outside = a.outside;
+    float *__restrict__ C = a.C;
+    const int64_t lda0 = a.lda0, lda1 = a.lda1, ldc = a.ldc;
+    const int32_t K = a.K, kt = a.kt, N = a.N;
+    const int relu = a.relu, vec = a.vec;
+    u32x4c *S = sh.stages;
+    float *s_max = sh.max;
+    Outlier *s_list = sh.list;
+    int &s_count = sh.count;
+    int *s_over = sh.over;
     const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (m_dev) M = *m_dev;
     const int64_t m0 = (int64_t)blockIdx.x * BM;
     if (m0 >= M) return;
     const int32_t T = 2 * kt, steps = T * kFrags;
@@ -531,7 +561,7 @@ __global__ void __launch_bounds__(64 * (kMulWaves + kRowWaves))
         const int x_s = __builtin_amdgcn_ds_permute(4 * rank, __builtin_bit_cast(int, o.x));
         // their rows of W, 32 columns each, all on the way together, then
         // through this wavefront's share of the stages (no longer read)
-        static_assert(kMulWaves * kListMax * 32 * sizeof(float) <= sizeof(S), "the list's weights fit the stages");
+        static_assert(kMulWaves * kListMax * 32 * sizeof(float) <= sizeof(sh.stages), "the list's weights fit the stages");
         float *wl = (float *)S + wid * (kListMax * 32);
         const int32_t col = g * 32 + lr < N ? g * 32 + lr : N - 1;
         float v[kListMax / 2];
@@ -578,6 +608,32 @@ __global__ void __launch_bounds__(64 * (kMulWaves + kRowWaves))
             }
         }
     }
+}
+
+template <int TM, int WM, int WN>
+__global__ void __launch_bounds__(64 * (kMulWaves + kRowWaves)) k_combine_f32(F32Args a) {
+    __shared__ F32Shared<32 * TM * WM> sh;
+    combine_f32_tile<TM, WM, WN>(a, a.m_dev ? *a.m_dev : a.M, sh);
+}
+
+// Rows of 32 on the busiest of `units` compute units (one workgroup each at a
+// time) with tiles of 32 blocks rows and `groups` column groups, half a
+// block's work of overhead a workgroup.
+__host__ __device__ inline int64_t f32_cost(int64_t m, int blocks, int64_t groups, int64_t units) {
+    const int64_t wgs = (m + 32 * blocks - 1) / (32 * blocks) * groups;
+    return (wgs + units - 1) / units * (2 * blocks + 1);
+}
+
+// The same for a row count on the device, with its tile height, 64 or 96 rows,
+// by the count and not by its bound: a sampled frontier's 20,900 rows under a
+// bound of 26,624 took 82 us in the two rounds of the bound's 64-row tiles.
+__global__ void __launch_bounds__(64 * (kMulWaves + kRowWaves)) k_combine_f32_counted(F32Args a, int32_t units) {
+    __shared__ F32Shared<96> sh;
+    const int64_t M = *a.m_dev;
+    if (f32_cost(M, 2, gridDim.y, units) < f32_cost(M, 3, gridDim.y, units))
+        combine_f32_tile<2, 1, 8>(a, M, (F32Shared<64> &)sh);
+    else
+        combine_f32_tile<3, 1, 8>(a, M, sh);
 }
 
 namespace {
@@ -627,36 +683,30 @@ void launch_combine_f32(const float *self, int64_t ld_self, const float *agg, in
     const int64_t kt = f32_kt(d_in), nc = f32_cols(d_out), values = nc * 2 * kt * kStep;
     const char *p = (const char *)ws;
     const int vec = ld_out % 4 == 0 && ((uintptr_t)out & 15u) == 0;
-    auto run = [&](auto tm_, auto wm_, auto wn_) {
-        constexpr int tm = decltype(tm_)::value, wm = decltype(wm_)::value, wn = decltype(wn_)::value;
-        const dim3 grid((unsigned)((m + 32 * tm * wm - 1) / (32 * tm * wm)), (unsigned)((d_out + 32 * wn - 1) / (32 * wn)));
-        hipLaunchKernelGGL((k_combine_f32<tm, wm, wn>), grid, dim3(64 * (kMulWaves + kRowWaves)), 0, s, self, ld_self, agg,
-                           ld_agg, m, m_dev, (int32_t)d_in, (int32_t)kt, w, (const u32x4c *)p,
-                           (const u32x4c *)(p + 4 * values), (const float *)(p + 10 * values),
-                           (const int32_t *)(p + 10 * values + 4 * nc), (int32_t)d_out, (int)relu, vec, out, ld_out);
-    };
-    const std::integral_constant<int, 1> i1;
-    const std::integral_constant<int, 2> i2;
-    const std::integral_constant<int, 3> i3;
-    const std::integral_constant<int, 4> i4;
-    const std::integral_constant<int, 8> i8;
-    // rows of 32 on the busiest compute unit (one workgroup each at a time),
-    // half a block's work of overhead a workgroup
+    const F32Args a{self, ld_self, agg, ld_agg, m, m_dev, (int32_t)d_in, (int32_t)kt, w, (const u32x4c *)p,
+                    (const u32x4c *)(p + 4 * values), (const float *)(p + 10 * values),
+                    (const int32_t *)(p + 10 * values + 4 * nc), (int32_t)d_out, (int)relu, vec, out, ld_out};
+    const dim3 threads(64 * (kMulWaves + kRowWaves));
+    auto grid = [&](int rows, int cols) { return dim3((unsigned)((m + rows - 1) / rows), (unsigned)((d_out + cols - 1) / cols)); };
     const int64_t units = stream_units(s);
-    auto cost = [&](int blocks, int wn) {
-        const int64_t wgs = ((m + 32 * blocks - 1) / (32 * blocks)) * ((d_out + 32 * wn - 1) / (32 * wn));
-        return (wgs + units - 1) / units * (2 * blocks + 1);
-    };
     if (d_out > 128) {
+        const int64_t groups = (d_out + 255) / 256;
         int best = 3;
         for (int b = 2; b >= 1; --b)
-            if (cost(b, 8) < cost(best, 8)) best = b;
-        if (best == 3) run(i3, i1, i8);
-        else if (best == 2) run(i2, i1, i8);
-        else run(i1, i1, i8);
+            if (f32_cost(m, b, groups, units) < f32_cost(m, best, groups, units)) best = b;
+        if (best == 1)
+            hipLaunchKernelGGL((k_combine_f32<1, 1, 8>), grid(32, 256), threads, 0, s, a);
+        else if (m_dev)
+            hipLaunchKernelGGL(k_combine_f32_counted, grid(64, 256), threads, 0, s, a, (int32_t)units);
+        else if (best == 2)
+            hipLaunchKernelGGL((k_combine_f32<2, 1, 8>), grid(64, 256), threads, 0, s, a);
+        else
+            hipLaunchKernelGGL((k_combine_f32<3, 1, 8>), grid(96, 256), threads, 0, s, a);
     } else {
-        if (cost(2, 4) < cost(4, 4)) run(i1, i2, i4);
-        else run(i2, i2, i4);
+        if (f32_cost(m, 2, 1, units) < f32_cost(m, 4, 1, units))
+            hipLaunchKernelGGL((k_combine_f32<1, 2, 4>), grid(64, 128), threads, 0, s, a);
+        else
+            hipLaunchKernelGGL((k_combine_f32<2, 2, 4>), grid(128, 128), threads, 0, s, a);
     }
     GNNAV_HIP(hipGetLastError());
 }

@@ -2,9 +2,10 @@
 // self * W[0:d_in] + agg * W[d_in:2*d_in] with two A-operand pointers, so
 // the concatenation is never stored.
 //
-// Matrix cores: fp32 runs on the fp16 matrix cores (combine_f32.hip) or, in
-// the hidden layers of a training step, on the bf16 matrix cores through a
-// three-way split of both operands (k_combine_split; both fp32-accurate);
+// Matrix cores: fp32 runs on the fp16 matrix cores (combine_f32.hip) or, for
+// narrow outputs, short rows and the hidden layers of a training step, on the
+// bf16 matrix cores through a three-way split of both operands
+// (k_combine_split; both fp32-accurate);
 // the backward product dX = dZ * W^T (launch_matmul_bt) uses
 // v_mfma_f32_32x32x2_f32 in the ring kernel; bf16 uses
 // v_mfma_f32_32x32x16_bf16 (ring) or v_mfma_f32_16x16x32_bf16 (skinny) with
@@ -714,9 +715,9 @@ static int64_t tail_split_bands(int64_t m, int64_t n, int64_t k) {
 // rows 103 -> 101, 20902 rows 117 -> 113, 26600 rows 154 -> 138.
 static int tail_pieces(int64_t tail_tiles) { return tail_tiles <= 192 ? 3 : 2; }
 
-// fp32 hidden layers of a training step (see launch_combine): the weights are
-// split into three bf16 parts and transposed, then k_combine_split runs; bf16:
-// the weights are transposed and padded, then the ring kernel runs.
+// fp32 by six products (see launch_combine): the weights are split into three
+// bf16 parts and transposed, then k_combine_split runs; bf16: the weights are
+// transposed and padded, then the ring kernel runs.
 template <int BM, int BN>
 static void launch_main(const void *self, int64_t ld_self, const void *agg, int64_t ld_agg, int64_t m,
                         const int32_t *m_dev, int64_t k, const void *w, int64_t n, bool bf16, bool relu,
@@ -851,7 +852,7 @@ int combine_kernel_kind(int64_t m, int64_t d_out, bool bf16) {
 // value within rounding of zero (expected once in some ten million) moves the
 // weight gradients of the layer below by 1e-5, and a step resumed or repeated
 // with another rounding would leave its trajectory.  Everything else, where a
-// rounding moves results by a rounding, takes the faster kernel.
+// rounding moves results by a rounding, takes the faster kernel for its sizes.
 void launch_combine(const void *self, int64_t ld_self, const void *agg, int64_t ld_agg, int64_t m,
                     const int32_t *m_dev, int64_t d_in, const void *w, int64_t d_out, bool bf16, bool relu, bool out_bf16, void *out,
                     int64_t ld_out, hipStream_t s, const char *label, bool six_products) {

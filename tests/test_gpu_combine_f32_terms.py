@@ -130,3 +130,31 @@ def test_edges(G, m, d_in, d_out, ld_extra, relu):
     got = _combine(G, S, A, Wt, relu, ld_extra)
     err = np.linalg.norm(got - (np.maximum(z, 0) if relu else z), axis=1) / scale
     assert err.max() <= TERM_TOL, f"row {int(err.argmax())} off by {err.max():.3e}"
+
+
+@pytest.mark.parametrize("n", [60_000, 20_000])
+def test_rows_counted_on_the_device(G, n):
+    """An asynchronous sample leaves the row count on the device, where the tile
+    height is chosen by it (96 rows for some 21,000 of a bound of 26,624, 64 for
+    some 14,000): the same bits as with the count on the host."""
+    import torch
+    from test_gpu_parity import dev, graph_case, host, padded
+    say("combine f32 counted", n)
+    _, u, v = graph_case(f"random-{n}-{n * 40}-3")
+    g = G.Graph(n, u, v)
+    rng = np.random.default_rng(n)
+    x = dev(padded(rng.standard_normal((n, 70)).astype(np.float32), "f32"))
+    dims = [70, 256, 41]
+    ws = [dev(W.glorot(a, b, "f32", seed=a)) for a, b in zip(dims[:-1], dims[1:])]
+    seeds = dev(rng.permutation(n)[:1024].astype(np.int32))
+    out = []
+    for call in (G.sample, G.sample_async):
+        blk = G.Blocks()
+        call(g, seeds, [25, 10], 7, blk)
+        logits = torch.zeros((1024, 41), device="cuda")
+        G.sage_forward(blk, x, ws, dims, "f32", logits)
+        torch.cuda.synchronize()
+        blk.sync()
+        say("rows", blk.sizes()[0])
+        out.append(host(logits))
+    assert out[0].any() and np.array_equal(*out)

@@ -375,13 +375,14 @@ def test_aggregate_mean_parity(G, d, dtype):
 
 # Small M runs the skinny kernel (fewer than 160 64x64 tiles; 16 wavefronts
 # per 16x16 output while there are at most 512 of those, else 8: 8000 and
-# 2100 rows here).  Larger M: fp32 runs the split-bf16 kernel on 128x128 or
-# 64x64 tiles (both taken here, e.g. 20000 x 602 x 256 and 40000 x 37 x
-# 130), bf16 the ring kernel on 128x64 / 64x64 / 128x128 tiles.  K tails:
-# d_in not a multiple of the 32 (fp32) or 64 (bf16) k step; ragged M and N.
-# fp32 tail split (d_in >= 128, 256 < 128x128 tiles <= 640), three k-pieces
-# per tail tile: 20000 x 602 x 256, 24001 x 300 x 250, 40000 x 128 x 100 (one
-# tile column); two: 33000 x 300 x 256, 20000 x 160 x 300 (three columns).
+# 2100 rows here).  Larger M: fp32 runs the kernel of two fp16 parts (20000 x
+# 602 x 256, 66000 x 100 x 256, 24001 x 300 x 250, ...) or, for narrow outputs
+# and short rows, the split-bf16 kernel on 128x128 or 64x64 tiles (40000 x 37 x
+# 130, 12000 x 64 x 41, ...); bf16 the streaming kernel or the ring on 128x64 /
+# 64x64 / 128x128 tiles.  K tails: d_in not a multiple of the 32 (fp32) or 64
+# (bf16) k step; ragged M and N.  Tail split of the split-bf16 kernel (d_in >=
+# 128, 256 < 128x128 tiles <= 640): three k-pieces per tail tile 40000 x 128 x
+# 100 (one tile column), two 20000 x 160 x 300 (three columns).
 COMBINE_CASES = [(1, 3, 16), (63, 64, 41), (64, 100, 47), (65, 602, 256), (1000, 128, 64),
                  (777, 256, 256), (130, 5, 300), (20000, 602, 256), (12000, 64, 41),
                  (12001, 100, 100), (9000, 256, 256), (10240, 3, 47), (6000, 128, 260),
