@@ -554,10 +554,11 @@ def kernel_entries(args, G, g, c, wl, fwd, seeds_dev, ring, link, profiled_confi
             gemm_bytes[kg] = gemm_bytes.get(kg, 0.0) + (n_dst * 2 * din + 2 * din * dout) * elt + n_dst * dout * out_elt
     probe.close()
     work.update(samp)
-    gemm_kind = {}
+    gemm_kind, products = {}, {}
     for l in range(1, L + 1):
         m_mean = max(1, int(round(float(np.mean(fwd["n_h"][:, L - l])))))
         gemm_kind[f"combine_gemm.l{l}"] = G.combine_kernel(m_mean, wl.dims[l], wl.dtype)
+        products[f"combine_gemm.l{l}"] = split_products(m_mean, wl.dims[l - 1], wl.dims[l])
     link_bound = miss_bytes > 0
     work["gather_rows"] = miss_bytes if link_bound else hit_bytes
 
@@ -578,13 +579,14 @@ def kernel_entries(args, G, g, c, wl, fwd, seeds_dev, ring, link, profiled_confi
         if name == "gather_rows" and link_bound:
             bound, peak, unit, amount = "host_link", HOST_LINK_PEAK_GBS, "GB/s", work[name]
         elif name.startswith("combine_gemm"):
-            # the algorithmic flops (2*M*K*N) against the peak of the precision
-            # the result carries (the split kernel computes fp32 products on
-            # the bf16 matrix cores; its executed bf16 work is a side figure);
-            # HBM-bound below the ridge point of that peak
-            ridge = MFMA_PEAK_TFLOPS[wl.dtype] * 1e12 / (HBM_PEAK_GBS * 1e9)
+            # the algorithmic flops (2*M*K*N) against the peak of the matrix
+            # cores that run them: a split kernel's fp32 products take three or
+            # six products of 16-bit parts, so a third or a sixth of the 16-bit
+            # peak; HBM-bound below the ridge point of that peak
+            tf_peak = round(MFMA_PEAK_TFLOPS["bf16"] / products[name], 1) if split else MFMA_PEAK_TFLOPS[wl.dtype]
+            ridge = tf_peak * 1e12 / (HBM_PEAK_GBS * 1e9)
             if work[name] / max(gemm_bytes.get(name, 1.0), 1.0) >= ridge:
-                bound, peak, unit, amount = "mfma", MFMA_PEAK_TFLOPS[wl.dtype], "TFLOP/s", work[name]
+                bound, peak, unit, amount = "mfma", tf_peak, "TFLOP/s", work[name]
             else:
                 bound, peak, unit, amount = "hbm", HBM_PEAK_GBS, "GB/s", gemm_bytes[name]
         else:
@@ -622,10 +624,11 @@ def kernel_entries(args, G, g, c, wl, fwd, seeds_dev, ring, link, profiled_confi
             ent["tflops"] = round(work[name] / (ms * 1e-3) / 1e12, 2)
             ent["flop_per_byte"] = round(work[name] / max(gemm_bytes.get(name, 1.0), 1.0), 1)
             if split:
-                ex = 3 * work[name] / (ms * 1e-3) / 1e12
-                ent["method"] = "fp32 products as three fp16 part products on the fp16 matrix cores"
-                ent["executed_f16_tflops"] = round(ex, 2)
-                ent["executed_frac_of_f16_peak"] = round(ex / MFMA_PEAK_TFLOPS["bf16"], 4)
+                ex = products[name] * work[name] / (ms * 1e-3) / 1e12
+                ent["method"] = ("fp32 products as three fp16 part products" if products[name] == 3 else
+                                 "fp32 products as six bf16 part products") + " on the 16-bit matrix cores"
+                ent["executed_16bit_tflops"] = round(ex, 2)
+                ent["executed_frac_of_16bit_peak"] = round(ex / MFMA_PEAK_TFLOPS["bf16"], 4)
         if name == "gather_rows":
             ent["hit_bytes_per_launch"] = round(hit_bytes / max(launches, 1), 1)
             if link_bound:
@@ -638,12 +641,25 @@ def kernel_entries(args, G, g, c, wl, fwd, seeds_dev, ring, link, profiled_confi
                            "gemm_kind": gemm_kind}
 
 
+def split_products(m: int, d_in: int, d_out: int) -> int:
+    """Part products per fp32 product of a "split" combine, by the rule of
+    combine_f32_parts in csrc/combine_f32.hip (three fp16 ones, else six bf16
+    ones); assumes no tile of the three leaves the fp16 parts' range."""
+    if d_in <= 64 or d_out <= 64:
+        return 6
+    if d_out <= 128:
+        parts = d_in > 256 or m <= 256 * 128
+    else:
+        parts = d_out <= 256 or d_in > 256 or 4 * d_out > 3 * (-(-d_out // 256) * 256)
+    return 3 if parts else 6
+
+
 def roofline_of(kernels, name, trace_name, profiled_config):
     k = kernels[name]
     rec = traffic_for(name, trace_name) if profiled_config else None
     out = {"kernel": name, "bound": k["bound"], "achieved": k["achieved"], "peak": k["peak"], "unit": k["unit"],
            "frac": k["frac"], "traffic": rec.get("bytes_per_launch") if rec else None}
-    for key in ("method", "executed_f16_tflops", "executed_frac_of_f16_peak", "frac_of_measured_link",
+    for key in ("method", "executed_16bit_tflops", "executed_frac_of_16bit_peak", "frac_of_measured_link",
                 "hit_bytes_per_launch", "algorithmic_bytes_per_launch", "useful_byte_efficiency",
                 "io_read_bytes_per_launch",
                 "io_read_gbs_counted", "dram_read_bytes_per_launch", "dram_write_bytes_per_launch"):

@@ -1,9 +1,10 @@
-"""The fp32 combine of many rows (two fp16 parts per value, three products) at
-the edges of its tiles and of its number range: rows, widths and columns around
+"""The fp32 combine of many rows (three products of two fp16 parts per value, or
+six of three bf16 parts, as the sizes say) at the edges of its tiles and of its
+number range: rows, widths and columns around
 one block, step and column group; NaN in the row padding; output rows that are
 not 16-byte aligned, with guard words; and data whose rows, columns or halves
-differ by powers of two up to 2^60, where tiles must fall back to the bf16
-split.  Against float64, 1e-5 per row as everywhere."""
+differ by powers of two up to 2^60, where tiles of the fp16 parts must fall back
+to the bf16 split.  Against float64, 1e-5 per row as everywhere."""
 import numpy as np
 import pytest
 
