@@ -54,11 +54,12 @@ def test_scales_are_undone_without_overflow(G, m, d_in, d_out, x, w):
 @pytest.mark.parametrize("m,d_in,d_out", MANY + FEW)
 @pytest.mark.parametrize("half", ["self", "agg", "both"])
 @pytest.mark.parametrize("columns", [1, 5])
-@pytest.mark.parametrize("p", [10, 20, 30, 40])
+@pytest.mark.parametrize("p", [-24, -21, 10, 20, 30, 40])
 def test_raw_columns_with_weights_to_match(G, m, d_in, d_out, half, columns, p):
-    """A few features 2^p times the others, their weights 2^-p times."""
+    """A few features 2^p times the others, their weights 2^-p times (2^-21 and
+    2^-24: at the lower end of the fp16 parts, the low ones subnormal)."""
     say("combine f32 raw columns", m, d_in, d_out, half, columns, p)
-    rng, S, A, Wt = _inputs(m, d_in, d_out, p)
+    rng, S, A, Wt = _inputs(m, d_in, d_out, abs(p))
     for x, w, name in ((S, Wt[:d_in], "self"), (A, Wt[d_in:], "agg")):
         if half in (name, "both"):
             k = rng.choice(d_in, columns, replace=False)
